@@ -38,6 +38,7 @@ struct pros_handle {
   bool coop = true;        // cooperative launch (co-residency guaranteed) or an ordinary dispatch
   long long* trace = nullptr;   // optional per-tile timestamps (diagnostics)
   bool mask_stale = true;       // mask not yet computed from the latest labels
+  unsigned char* pin = nullptr; // pinned host memory: header (error bits, statistics), then a mask of P bytes
   long long timeout_ticks = 0;
   // frames too large for a resident gang: every pass streams U (prost_stream.hip)
   bool streamed = false;
@@ -64,7 +65,8 @@ pros_status create_handle(const pros_params* prm, hipStream_t stream, int nr_for
                           pros_handle** out);
 void free_handle(pros_handle* h);
 pros_status check_usable(pros_handle* h);
-pros_status sync_and_check(pros_handle* h);
+pros_status sync_and_check(pros_handle* h, bool from_header = false);
+constexpr int kPinHeader = 512;   // bytes in front of the mask in pros_handle::pin: error bits, statistics at 16
 prost::FrameArgs make_args(pros_handle* h, const void* x);
 pros_status reset_exchange(pros_handle* h);
 // Compute the mask (and foreground count) of the latest labels if a frame

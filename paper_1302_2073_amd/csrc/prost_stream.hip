@@ -605,6 +605,7 @@ __global__ __launch_bounds__(kStBlock) void st_update(FrameArgs a, const StreamK
 // Frame end: y and the frame counter (an accepted frame only).
 __global__ void st_end(FrameArgs a, const StreamKS* __restrict__ ks) {
   const int t = threadIdx.x;
+  if (t == 0) a.sync[4] = 0;   // the mask is no longer the labels' median
   if (ks->bad) {
     if (t == 0) a.stats->bad_frame = 1;
     return;
