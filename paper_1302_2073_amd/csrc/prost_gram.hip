@@ -6,9 +6,10 @@
 //   U <- U G^{-1/2},  G = U^T U,
 // and y <- G^{1/2} y keeps U y unchanged to first order.  Three kernels:
 //   gram_partial: per-workgroup float64 partial sums of the upper triangle of G
-//   gram_solve:   one wavefront: fixed-order sum, cyclic Jacobi eigensolver of
-//                 G (float64), G^{-1/2}, G^{1/2}, y update
-//   gram_apply:   u_e <- u_e G^{-1/2} row by row in float64, rounded to storage
+//   gram_solve:   fixed-order sum, Jacobi eigensolver of G in one wavefront
+//                 (float64), G^{-1/2}, G^{1/2} y
+//   gram_apply:   u_e <- u_e G^{-1/2} in float64, rounded to storage
+// Both passes over U run their products on the float64 matrix instruction.
 #include <hip/hip_runtime.h>
 
 #include "prost_device.hpp"
@@ -16,173 +17,289 @@
 
 namespace prost {
 
-constexpr int kGramRows = 256;                  // rows per LDS tile
 constexpr int kGramPairs = kMaxK * (kMaxK + 1) / 2;
-constexpr int kGramBlocks = 512;
+constexpr int kGramBlocks = 256;      // one workgroup of 8 wavefronts per compute unit
+constexpr int kGramThreads = 512;
+constexpr int kGramWaves = kGramThreads / 64;
+constexpr int kSolveThreads = 1024;
+
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
+// Elements of one column that a lane takes at a time: 16 bytes of the storage
+// types (their planes are 16-byte aligned), one of the float64 initialization
+// matrix (its planes are m apart, m arbitrary).
+template <typename TS>
+constexpr int gram_vec() { return sizeof(TS) == 8 ? 1 : 16 / (int)sizeof(TS); }
 
 template <typename TS>
-__global__ __launch_bounds__(256) void gram_partial(const TS* __restrict__ U, long long ldU, int m, int k,
-                                                    double* __restrict__ part) {
-  __shared__ double tile[kGramRows][kMaxK + 1];
-  // pair index -> (i, j), i <= j, fixed for the launch
-  int pi = -1, pj = -1;
-  {
-    int t = threadIdx.x, i = 0;
-    while (i < k && t >= k - i) { t -= k - i; ++i; }
-    if (i < k) { pi = i; pj = i + t; }
-  }
-  double acc = 0.0;
-  for (long long r0 = (long long)blockIdx.x * kGramRows; r0 < m; r0 += (long long)gridDim.x * kGramRows) {
-    const int rows = (int)min((long long)kGramRows, (long long)m - r0);
-    __syncthreads();
-    for (int j = 0; j < k; ++j) {
-      const int e = threadIdx.x;
-      tile[e][j] = (e < rows) ? (double)ld_elem(U, (long long)j * ldU + r0 + e) : 0.0;
-    }
-    __syncthreads();
-    if (pi >= 0) {
-      for (int e = 0; e < rows; ++e) acc = fma(tile[e][pi], tile[e][pj], acc);
+__device__ __forceinline__ void gram_load(const TS* __restrict__ col, long long r, long long m, bool on,
+                                          double (&v)[gram_vec<TS>()]) {
+  constexpr int V = gram_vec<TS>();
+  if constexpr (V > 1) {
+    if (on && r + V <= m) {
+      const uint4 w = *(const uint4*)(col + r);
+      const uint32_t q[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+      for (int i = 0; i < V; ++i)
+        v[i] = (double)(sizeof(TS) == 4 ? __uint_as_float(q[i & 3])
+                                        : __uint_as_float((i & 1) ? (q[i >> 1] & 0xFFFF0000u) : (q[i >> 1] << 16)));
+      return;
     }
   }
-  if (threadIdx.x < kGramPairs) part[(size_t)blockIdx.x * kGramPairs + threadIdx.x] = (pi >= 0) ? acc : 0.0;
+#pragma unroll
+  for (int i = 0; i < V; ++i) v[i] = (on && r + i < m) ? (double)ld_elem(col, r + i) : 0.0;
 }
 
-// One wavefront.  ws layout: [0, 256) G^{-1/2} (row-major k x k, stride 16).
-__global__ __launch_bounds__(64) void gram_solve(const double* __restrict__ part, int nblocks, int k,
-                                                 double* __restrict__ y, double* __restrict__ ws) {
-  __shared__ double A[kMaxK][kMaxK];
-  __shared__ double Vm[kMaxK][kMaxK];
-  __shared__ double cs[2];
-  const int l = threadIdx.x;
-  // fixed-order sum of the partials; thread owns pairs l, l+64, l+128
-  for (int q = l; q < kGramPairs; q += 64) {
-    double s = 0.0;
-    for (int b = 0; b < nblocks; ++b) s += part[(size_t)b * kGramPairs + q];
-    int t = q, i = 0;
-    while (i < k && t >= k - i) { t -= k - i; ++i; }
-    if (i < k) { A[i][i + t] = s; A[i + t][i] = s; }
+// Partial sums of the upper triangle of G = U^T U, pair (i, j) at
+// part[block * kGramPairs + ...], row by row.  G is a contraction over the rows
+// with both operands U: lane l holds column l % 16 of some rows in float64, and
+// v_mfma_f64_16x16x4 with that one register as both operands adds the products
+// of its four lane groups' rows (the order of rows within the sum is free, so a
+// lane's rows can be the 16 contiguous bytes that it loads).  Products are
+// exact in float64 and accumulation is float64, as before; the order is fixed.
+// Bound by the latency of the reads of U.  With a float64 LDS tile and one pair
+// per thread it was bound by LDS reads (640x480x3, k = 15, bfloat16: 63 us;
+// this form 18, and 22 in float32: 2.5 TB/s).
+template <typename TS>
+__global__ __launch_bounds__(kGramThreads) void gram_partial(const TS* __restrict__ U, long long ldU, long long m,
+                                                             int k, double* __restrict__ part) {
+  constexpr int V = gram_vec<TS>();
+  __shared__ double red[kGramWaves][256];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int j = lane & 15;
+  const bool on = j < k;
+  const TS* col = U + (long long)(on ? j : 0) * ldU;
+  f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
+  const long long step = (long long)gridDim.x * kGramWaves * 4 * V;
+  for (long long r0 = ((long long)blockIdx.x * kGramWaves + wv) * 4 * V; r0 < m; r0 += 2 * step) {
+    const long long r = r0 + (lane >> 4) * V;
+    double v0[V], v1[V];
+    gram_load(col, r, m, on, v0);
+    gram_load(col, r + step, m, on, v1);   // all zero past the end
+#pragma unroll
+    for (int i = 0; i < V; ++i) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v0[i], v0[i], acc, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < V; ++i) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v1[i], v1[i], acc, 0, 0, 0);
   }
-  if (l < kMaxK)
-    for (int j = 0; j < kMaxK; ++j) Vm[l][j] = (l == j) ? 1.0 : 0.0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) red[wv][(4 * i + (lane >> 4)) * 16 + j] = acc[i];   // row 4 i + lane / 16, column lane % 16
   __syncthreads();
-  // cyclic Jacobi: rotate (p, q) pairs until the off-diagonal mass vanishes
-  for (int sweep = 0; sweep < 30; ++sweep) {
-    double off = 0.0, dia = 0.0;
-    for (int i = 0; i < k; ++i)
-      for (int j = 0; j < k; ++j) {
-        if (i != j) off += A[i][j] * A[i][j];
-        else dia += A[i][j] * A[i][j];
-      }
-    if (!(off > 1e-32 * dia)) break;
-    for (int p = 0; p < k - 1; ++p) {
-      for (int q = p + 1; q < k; ++q) {
-        if (l == 0) {
-          const double apq = A[p][q];
-          double c = 1.0, s = 0.0;
-          if (apq != 0.0) {
-            const double tau = (A[q][q] - A[p][p]) / (2.0 * apq);
-            const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-            c = 1.0 / sqrt(1.0 + t * t);
-            s = t * c;
-          }
-          cs[0] = c;
-          cs[1] = s;
-        }
-        __syncthreads();
-        const double c = cs[0], s = cs[1];
-        if (s != 0.0) {
-          // A <- J^T A J with J the (p, q) rotation; V <- V J
-          if (l < k) {
-            const double akp = A[l][p], akq = A[l][q];
-            A[l][p] = c * akp - s * akq;
-            A[l][q] = s * akp + c * akq;
-          }
-          __syncthreads();
-          if (l < k) {
-            const double apk = A[p][l], aqk = A[q][l];
-            A[p][l] = c * apk - s * aqk;
-            A[q][l] = s * apk + c * aqk;
-            const double vkp = Vm[l][p], vkq = Vm[l][q];
-            Vm[l][p] = c * vkp - s * vkq;
-            Vm[l][q] = s * vkp + c * vkq;
-          }
-        }
-        __syncthreads();
-      }
+  if (threadIdx.x < 256) {
+    const int row = threadIdx.x >> 4, cl = threadIdx.x & 15;
+    if (row <= cl && cl < k) {
+      double s = 0.0;
+#pragma unroll
+      for (int w = 0; w < kGramWaves; ++w) s += red[w][threadIdx.x];
+      part[(size_t)blockIdx.x * kGramPairs + row * k - row * (row - 1) / 2 + (cl - row)] = s;
     }
   }
-  // G^{-1/2} = V diag(lam^{-1/2}) V^T, G^{1/2} = V diag(lam^{1/2}) V^T
-  __shared__ double lam[kMaxK];
-  __shared__ double yn[kMaxK];
-  __shared__ int degenerate;
-  if (l == 0) degenerate = 0;
-  __syncthreads();
-  if (l < k) {
-    lam[l] = A[l][l];
-    if (!(A[l][l] > 1e-300)) atomicOr(&degenerate, 1);
+}
+
+// Fixed-order sum of the workgroups' partials into the symmetric G (LDS), by
+// kSolveThreads threads: seven per pair, each every seventh workgroup, their
+// sums added in order.  (One wavefront with a pair per lane read 512 partials
+// one after the other: most of 0.1 ms.)
+__device__ __forceinline__ void gram_sum(const double* __restrict__ part, int nblocks, int k,
+                                         double (*G)[kMaxK], double* __restrict__ buf) {
+  constexpr int kGroups = kSolveThreads / kGramPairs;
+  const int np = k * (k + 1) / 2;
+  const int q = threadIdx.x % kGramPairs, g = threadIdx.x / kGramPairs;
+  if (g < kGroups && q < np) {
+    double s = 0.0;
+#pragma unroll 8
+    for (int b = g; b < nblocks; b += kGroups) s += part[(size_t)b * kGramPairs + q];
+    buf[g * kGramPairs + q] = s;
   }
   __syncthreads();
-  if (degenerate) {   // rank-deficient U: leave U and y unchanged
+  if (threadIdx.x < (unsigned)np) {
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i) s += buf[i * kGramPairs + threadIdx.x];
+    int t = threadIdx.x, i = 0;
+    while (t >= k - i) { t -= k - i; ++i; }
+    G[i][i + t] = s;
+    G[i + t][i] = s;
+  }
+  __syncthreads();
+}
+
+// Orders the LDS accesses of one wavefront (they execute in order; this keeps
+// the compiler from moving them).
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// G^{-1/2} into ws (row-major k x k, stride 16) and y <- G^{1/2} y, from an
+// eigendecomposition of G by Jacobi rotations in float64, one wavefront after
+// the sum of the partials.  The rotations of a sweep go in the round-robin
+// order: n / 2 disjoint pairs at a time (n: k rounded up to even), whose angles
+// n / 2 lanes form together and whose two-sided update is one 2 x 2 block per
+// lane.  The chain of divisions and roots is what bounds it, and it is paid
+// n - 1 times per sweep instead of k (k - 1) / 2 times: at k = 15 the kernel
+// took 825 us with one pair at a time and takes 57-72.
+__global__ __launch_bounds__(kSolveThreads) void gram_solve(const double* __restrict__ part, int nblocks, int k,
+                                                            double* __restrict__ y, double* __restrict__ ws) {
+  __shared__ double A[kMaxK][kMaxK];
+  __shared__ double Vm[kMaxK][kMaxK];
+  __shared__ double cs[kMaxK / 2][2];
+  __shared__ double buf[(kSolveThreads / kGramPairs) * kGramPairs];
+  if (threadIdx.x < kMaxK * kMaxK) {
+    const int i = threadIdx.x / kMaxK, j = threadIdx.x % kMaxK;
+    Vm[i][j] = (i == j) ? 1.0 : 0.0;
+    if (i >= k || j >= k) A[i][j] = (i == j) ? 1.0 : 0.0;   // pads an odd k: never rotated
+  }
+  gram_sum(part, nblocks, k, A, buf);
+  if (threadIdx.x >= 64) return;
+  const int l = threadIdx.x;
+  const int n = (k + 1) & ~1, half = n / 2;
+  const int bi = l >> 3, bj = l & 7;
+  for (int sweep = 0; sweep < 30 && k > 1; ++sweep) {
+    double off = 0.0, dia = 0.0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int i = l >> 2, j = 4 * (l & 3) + c;
+      const double v = (i < k && j < k) ? A[i][j] * A[i][j] : 0.0;
+      if (i == j) dia += v;
+      else off += v;
+    }
+    off = wave_sum(off);
+    dia = wave_sum(dia);
+    // what is left is rounding of the rotations themselves (entries near
+    // 2^-53 of the diagonal): a tighter bound is not reached when U is
+    // orthonormal already, and all 30 sweeps would run
+    if (!(off > 1e-30 * dia)) break;
+    for (int s = 0; s < n - 1; ++s) {
+      // pair i of step s: (n - 1, s) for i = 0, ((s + i) mod (n - 1), (s - i) mod (n - 1)) else
+      auto first = [&](int i) { return i == 0 ? n - 1 : s + i >= n - 1 ? s + i - (n - 1) : s + i; };
+      auto second = [&](int i) { return s - i < 0 ? s - i + n - 1 : s - i; };
+      if (l < half) {
+        const int p = first(l), q = second(l);
+        const double apq = A[p][q], th = A[q][q] - A[p][p], d = 2.0 * apq;
+        double c = 1.0, sn = 0.0;
+        if (apq != 0.0) {   // t = sgn(tau) / (|tau| + sqrt(1 + tau^2)), tau = th / d
+          const double t = (th >= 0.0 ? d : -d) / (fabs(th) + sqrt(fma(th, th, d * d)));
+          c = rsqrt(fma(t, t, 1.0));
+          sn = t * c;
+        }
+        cs[l][0] = c;
+        cs[l][1] = sn;
+      }
+      wave_fence();
+      if (bi < half && bj < half) {   // A <- J^T A J, the 2 x 2 block of pairs bi (rows) and bj (columns)
+        const int p = first(bi), q = second(bi), u = first(bj), v = second(bj);
+        const double ci = cs[bi][0], si = cs[bi][1], cj = cs[bj][0], sj = cs[bj][1];
+        const double a = A[p][u], b = A[p][v], c = A[q][u], d = A[q][v];
+        const double a1 = cj * a - sj * b, b1 = sj * a + cj * b;
+        const double c1 = cj * c - sj * d, d1 = sj * c + cj * d;
+        A[p][u] = ci * a1 - si * c1;
+        A[p][v] = ci * b1 - si * d1;
+        A[q][u] = si * a1 + ci * c1;
+        A[q][v] = si * b1 + ci * d1;
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {   // V <- V J, row l % 16, pairs l / 16 and l / 16 + 4
+        const int i = (l >> 4) + 4 * h, r = l & 15;
+        if (i < half) {
+          const int p = first(i), q = second(i);
+          const double c = cs[i][0], sn = cs[i][1];
+          const double vp = Vm[r][p], vq = Vm[r][q];
+          Vm[r][p] = c * vp - sn * vq;
+          Vm[r][q] = sn * vp + c * vq;
+        }
+      }
+      wave_fence();
+    }
+  }
+  // G^{-1/2} = V diag(lam^{-1/2}) V^T, G^{1/2} y = V diag(lam^{1/2}) V^T y
+  const double lam = (l < k) ? A[l][l] : 1.0;
+  if (__any(!(lam > 1e-300))) {   // rank-deficient U: leave U and y unchanged
     if (l < k)
       for (int j = 0; j < k; ++j) ws[l * kMaxK + j] = (l == j) ? 1.0 : 0.0;
     return;
   }
+  double* root = buf;              // sqrt(lam), then its reciprocal at 16, V^T y scaled at 32
+  if (l < kMaxK) {
+    root[l] = sqrt(lam);
+    root[kMaxK + l] = 1.0 / sqrt(lam);
+  }
+  wave_fence();
   if (l < k) {
-    for (int j = 0; j < k; ++j) {
-      double mneg = 0.0;
-      for (int i = 0; i < k; ++i) mneg += Vm[l][i] * Vm[j][i] / sqrt(lam[i]);
-      ws[l * kMaxK + j] = mneg;
-    }
-    double s = 0.0;
-    for (int j = 0; j < k; ++j) {
-      double mpos = 0.0;
-      for (int i = 0; i < k; ++i) mpos += Vm[l][i] * Vm[j][i] * sqrt(lam[i]);
-      s += mpos * y[j];
-    }
-    yn[l] = s;
+    double t = 0.0;
+    for (int i = 0; i < k; ++i) t = fma(Vm[i][l], y[i], t);
+    root[2 * kMaxK + l] = root[l] * t;
   }
-  __syncthreads();
-  if (l < k) y[l] = yn[l];
-}
-
-template <int K, typename TS>
-__global__ __launch_bounds__(256) void gram_apply(TS* __restrict__ U, long long ldU, int m,
-                                                  const double* __restrict__ ws) {
-  __shared__ double M[K][K];
-  for (int q = threadIdx.x; q < K * K; q += 256) M[q / K][q % K] = ws[(q / K) * kMaxK + (q % K)];
-  __syncthreads();
-  for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < m; e += (long long)gridDim.x * 256) {
-    // an offset the compiler cannot see is zero: the LDS reads of M stay in
-    // the loop instead of being hoisted into (K * K * 2) registers and spilled
-    int z = 0;
-    asm volatile("" : "+v"(z));
-    const double* Ml = &M[0][0] + z;
-    double u[K];
-#pragma unroll
-    for (int i = 0; i < K; ++i) u[i] = (double)ld_elem(U, (long long)i * ldU + e);
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      double s = 0.0;
-#pragma unroll
-      for (int i = 0; i < K; ++i) s = fma(u[i], Ml[i * K + j], s);
-      st_elem(U, (long long)j * ldU + e, (float)s);
-    }
+  wave_fence();
+  for (int q = l; q < k * k; q += 64) {
+    const int i = q / k, j = q - i * k;
+    double t = 0.0;
+    for (int c = 0; c < k; ++c) t = fma(Vm[i][c] * root[kMaxK + c], Vm[j][c], t);
+    ws[i * kMaxK + j] = t;
+  }
+  if (l < k) {
+    double t = 0.0;
+    for (int c = 0; c < k; ++c) t = fma(Vm[l][c], root[2 * kMaxK + c], t);
+    y[l] = t;
   }
 }
 
+// u_e <- u_e G^{-1/2} for every row, in float64, rounded to the storage type.
+// The transposed product M^T U^T goes through v_mfma_f64_16x16x4: M (symmetric)
+// stays in four registers, and the result has lane l % 16 = row, so a lane
+// that takes two adjacent rows stores them as one word into each plane.  Bound
+// by the read and the write of U; with one row per thread it was bound by the
+// K^2 reads of M from LDS per row (640x480x3, k = 15, bfloat16: 31 us; now 21).
 template <typename TS>
-static hipError_t launch_apply(int k, TS* U, long long ldU, int m, const double* ws, int blocks, hipStream_t st) {
-#define PROST_APPLY_CASE(KK) \
-  case KK: hipLaunchKernelGGL((gram_apply<KK, TS>), dim3(blocks), dim3(256), 0, st, U, ldU, m, ws); break;
-  switch (k) {
-    PROST_APPLY_CASE(1) PROST_APPLY_CASE(2) PROST_APPLY_CASE(3) PROST_APPLY_CASE(4)
-    PROST_APPLY_CASE(5) PROST_APPLY_CASE(6) PROST_APPLY_CASE(7) PROST_APPLY_CASE(8)
-    PROST_APPLY_CASE(9) PROST_APPLY_CASE(10) PROST_APPLY_CASE(11) PROST_APPLY_CASE(12)
-    PROST_APPLY_CASE(13) PROST_APPLY_CASE(14) PROST_APPLY_CASE(15) PROST_APPLY_CASE(16)
-    default: return hipErrorInvalidValue;
+__global__ __launch_bounds__(256) void gram_apply(TS* __restrict__ U, long long ldU, int m, int k,
+                                                  const double* __restrict__ ws) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lo = lane & 15, hi = lane >> 4;
+  double M[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) M[s] = (4 * s + hi < k && lo < k) ? ws[(4 * s + hi) * kMaxK + lo] : 0.0;
+  for (long long r0 = ((long long)blockIdx.x * 4 + wv) * 32; r0 < m; r0 += (long long)gridDim.x * 128) {
+    const long long r = r0 + 2 * lo;   // rows r, r + 1 (one word of every plane: ldU is a multiple of 64)
+    const bool in = r < m;
+    double u[4][2];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      float a = 0.f, b = 0.f;
+      if (in && 4 * s + hi < k) {
+        const TS* p = U + (long long)(4 * s + hi) * ldU + r;
+        if constexpr (sizeof(TS) == 2) {
+          const uint32_t w = *(const uint32_t*)p;
+          a = __uint_as_float(w << 16);
+          b = __uint_as_float(w & 0xFFFF0000u);
+        } else {
+          const float2 w = *(const float2*)p;
+          a = w.x;
+          b = w.y;
+        }
+      }
+      u[s][0] = (double)a;
+      u[s][1] = (double)b;
+    }
+    f64x4_t d0 = {0.0, 0.0, 0.0, 0.0}, d1 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      d0 = __builtin_amdgcn_mfma_f64_16x16x4f64(M[s], u[s][0], d0, 0, 0, 0);
+      d1 = __builtin_amdgcn_mfma_f64_16x16x4f64(M[s], u[s][1], d1, 0, 0, 0);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {      // column 4 c + lane / 16 of rows r, r + 1
+      const int j = 4 * c + hi;
+      if (!in || j >= k) continue;
+      TS* p = U + (long long)j * ldU + r;
+      if (r + 1 < m) {
+        if constexpr (sizeof(TS) == 2)
+          *(uint32_t*)p = (uint32_t)f32_to_bf16_rne((float)d0[c]) | ((uint32_t)f32_to_bf16_rne((float)d1[c]) << 16);
+        else
+          *(float2*)p = make_float2((float)d0[c], (float)d1[c]);
+      } else {
+        st_elem(p, 0, (float)d0[c]);
+      }
+    }
   }
-#undef PROST_APPLY_CASE
-  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -234,23 +351,17 @@ __global__ __launch_bounds__(256) void gauss_fill(double* __restrict__ A, long l
   }
 }
 
-// One wavefront: G from the partials (fixed order), Cholesky G = R^T R (R
+// G from the partials (fixed order), Cholesky G = R^T R (R
 // upper, by lane 0 in float64), R^{-1} (upper) into ws (k x k, stride 16).
 // A non-positive pivot (rank-deficient A) sets *bad and leaves ws = I.
-__global__ __launch_bounds__(64) void qr_chol_inv(const double* __restrict__ part, int nblocks, int k,
+__global__ __launch_bounds__(kSolveThreads) void qr_chol_inv(const double* __restrict__ part, int nblocks, int k,
                                                   double* __restrict__ ws, int* __restrict__ bad) {
   __shared__ double G[kMaxK][kMaxK];
   __shared__ double R[kMaxK][kMaxK];
   __shared__ double Ri[kMaxK][kMaxK];
+  __shared__ double buf[(kSolveThreads / kGramPairs) * kGramPairs];
   const int l = threadIdx.x;
-  for (int q = l; q < kGramPairs; q += 64) {
-    double s = 0.0;
-    for (int b = 0; b < nblocks; ++b) s += part[(size_t)b * kGramPairs + q];
-    int t = q, i = 0;
-    while (i < k && t >= k - i) { t -= k - i; ++i; }
-    if (i < k) { G[i][i + t] = s; G[i + t][i] = s; }
-  }
-  __syncthreads();
+  gram_sum(part, nblocks, k, G, buf);
   if (l == 0) {
     int ok = 1;
     for (int i = 0; i < k && ok; ++i) {
@@ -339,7 +450,7 @@ pros_status prost_random_subspace(unsigned long long seed, uint32_t stream_index
                                   hipStream_t st) {
   using namespace prost;
   if (m < k || k < 1 || k > PROS_MAX_K) return prost_host::set_error(PROS_EINVAL, "need 1 <= k <= min(m, %d)", PROS_MAX_K);
-  const int nb = (int)std::min<long long>(kGramBlocks, (m + kGramRows - 1) / kGramRows);
+  const int nb = (int)std::min<long long>(kGramBlocks, (m + 255) / 256);
   double* part = nullptr;
   hipError_t e = hipMalloc((void**)&part, sizeof(double) * ((size_t)kGramBlocks * kGramPairs + 256) + 64);
   if (e != hipSuccess) return prost_host::set_error(PROS_ENOMEM, "initialization scratch: %s", hipGetErrorString(e));
@@ -352,8 +463,8 @@ pros_status prost_random_subspace(unsigned long long seed, uint32_t stream_index
   if (e == hipSuccess) {
     hipLaunchKernelGGL(gauss_fill, dim3(fb), dim3(256), 0, st, A, n, seed, stream_index);
     for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {
-      hipLaunchKernelGGL((gram_partial<double>), dim3(nb), dim3(256), 0, st, (const double*)A, m, (int)m, k, part);
-      hipLaunchKernelGGL(qr_chol_inv, dim3(1), dim3(64), 0, st, (const double*)part, nb, k, ws, bad);
+      hipLaunchKernelGGL((gram_partial<double>), dim3(nb), dim3(kGramThreads), 0, st, (const double*)A, m, m, k, part);
+      hipLaunchKernelGGL(qr_chol_inv, dim3(1), dim3(kSolveThreads), 0, st, (const double*)part, nb, k, ws, bad);
       e = qr_apply_launch(k, A, m, ws, ab, st);
     }
   }
@@ -391,7 +502,7 @@ pros_status prost_init_subspace(pros_handle* h, unsigned long long seed, uint32_
 
 pros_status prost_reorth_launch(pros_handle* h) {
   using namespace prost;
-  const int nb = (int)std::min<long long>(kGramBlocks, ((long long)h->m + kGramRows - 1) / kGramRows);
+  const int nb = (int)std::min<long long>(kGramBlocks, ((long long)h->m + 255) / 256);
   if (!h->reorth_ws) {
     hipError_t e = hipMalloc(&h->reorth_ws, sizeof(double) * ((size_t)kGramBlocks * kGramPairs + 256));
     if (e != hipSuccess) return prost_host::set_error(PROS_ENOMEM, "re-orthonormalisation workspace: %s", hipGetErrorString(e));
@@ -400,13 +511,20 @@ pros_status prost_reorth_launch(pros_handle* h) {
   double* ws = part + (size_t)kGramBlocks * kGramPairs;
   const bool bf = h->prm.storage == PROS_BF16;
   if (bf)
-    hipLaunchKernelGGL((gram_partial<uint16_t>), dim3(nb), dim3(256), 0, h->stream, (const uint16_t*)h->U, h->ldU, h->m, h->k, part);
+    hipLaunchKernelGGL((gram_partial<uint16_t>), dim3(nb), dim3(kGramThreads), 0, h->stream, (const uint16_t*)h->U, h->ldU,
+                       (long long)h->m, h->k, part);
   else
-    hipLaunchKernelGGL((gram_partial<float>), dim3(nb), dim3(256), 0, h->stream, (const float*)h->U, h->ldU, h->m, h->k, part);
-  hipLaunchKernelGGL(gram_solve, dim3(1), dim3(64), 0, h->stream, (const double*)part, nb, h->k, h->y, ws);
-  const int ab = (int)std::min<long long>(2048, ((long long)h->m + 255) / 256);
-  hipError_t e = bf ? launch_apply<uint16_t>(h->k, (uint16_t*)h->U, h->ldU, h->m, ws, ab, h->stream)
-                    : launch_apply<float>(h->k, (float*)h->U, h->ldU, h->m, ws, ab, h->stream);
+    hipLaunchKernelGGL((gram_partial<float>), dim3(nb), dim3(kGramThreads), 0, h->stream, (const float*)h->U, h->ldU,
+                       (long long)h->m, h->k, part);
+  hipLaunchKernelGGL(gram_solve, dim3(1), dim3(kSolveThreads), 0, h->stream, (const double*)part, nb, h->k, h->y, ws);
+  const int ab = (int)std::min<long long>(2048, ((long long)h->m + 127) / 128);
+  if (bf)
+    hipLaunchKernelGGL((gram_apply<uint16_t>), dim3(ab), dim3(256), 0, h->stream, (uint16_t*)h->U, h->ldU, h->m, h->k,
+                       (const double*)ws);
+  else
+    hipLaunchKernelGGL((gram_apply<float>), dim3(ab), dim3(256), 0, h->stream, (float*)h->U, h->ldU, h->m, h->k,
+                       (const double*)ws);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     h->broken = true;
     h->broken_status = PROS_EHIP;
