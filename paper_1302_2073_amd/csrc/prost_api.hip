@@ -716,8 +716,12 @@ FrameArgs prost_host::make_args(pros_handle* h, const void* x) {
 // re-orthonormalisation when one is due after them.
 static pros_status launch_frames(pros_handle* h, FrameArgs& a, const void* fn) {
   void* args[] = {&a};
-  hipError_t e = h->coop ? hipLaunchCooperativeKernel(fn, dim3(h->G), dim3(prost::kBlock), args, 0, h->stream)
-                         : hipLaunchKernel(fn, dim3(h->G), dim3(prost::kBlock), args, 0, h->stream);
+  // A gang of one workgroup waits for nobody, so it needs no co-residency: the
+  // cooperative dispatch (a queue of its own behind barriers, 11 us before and
+  // 11 us after the kernel at 80x60x1) is left to gangs that exchange.
+  hipError_t e = h->coop && h->G > 1
+                     ? hipLaunchCooperativeKernel(fn, dim3(h->G), dim3(prost::kBlock), args, 0, h->stream)
+                     : hipLaunchKernel(fn, dim3(h->G), dim3(prost::kBlock), args, 0, h->stream);
   if (e != hipSuccess) {
     h->broken = true;
     h->broken_status = PROS_EHIP;
