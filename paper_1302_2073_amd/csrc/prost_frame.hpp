@@ -73,7 +73,9 @@ struct FrameArgs {
 };
 
 constexpr int kReplicas = 8;      // copies of a gathered result (spread the pollers)
-constexpr int kExtraSlots = 32;   // slots beyond 2 G: replicas / XCD-level slots
+constexpr int kGroups = 8;        // groups of the two-hop exchange
+// slots beyond 2 G: two alternating sets of the kGroups group sums in kReplicas copies
+constexpr int kExtraSlots = 2 * kGroups * kReplicas;
 
 // Shared k-space state of one workgroup (all float64 unless noted).
 constexpr int kMaxNR = 32;   // register rows per thread (bfloat16 pairs at small k)
@@ -86,6 +88,8 @@ struct KSpace {
   double a[K];      // U^T eta
   double red[kSlot];
   double gd;        // g . d of the current step
+  double gg;        // g . g of the latest gradient
+  double t;         // step size of this frame (Sec. 3.4)
   float df[K];      // direction (float) for the row passes
   float vf[K];      // v = y/||y||
   float af[K];      // a (float)
@@ -107,10 +111,13 @@ constexpr int kWideIn = kWideMax + kSlot;   // room for the last zero-padded chu
 
 struct FrameSmem {
   KSpace<kMaxK> ks;
-  double red[kWaves][kSlot];
+  double red[kWaves][kSlot];   // wavefront partials of a vector exchange
+  double red1[kWaves];         // ... of a single-value exchange
+  double got[kWaves][kSlot];   // gathered sums, one row per wavefront
+  double one;                  // total of a single-value exchange
   double wg[kSlot];
   double big[kBlock];          // one float64 per thread (gathers)
-  int ctl[4];
+  int ctl[4];                  // [2] the gang gave up waiting (checked after the barrier that follows an exchange)
   uint8_t flag[kBlock * kMaxNR];
   double wide_in[kWideIn];     // wide exchange: this workgroup's partials
   double wide_out[kWideMax];   // wide exchange: gang totals
@@ -234,85 +241,248 @@ __device__ __forceinline__ bool gang_reduce_tagged(const double* wg_sum, const F
   return s_ctl[1] == 0;
 }
 
-// Tagged all-read helper: waits for n tagged slots (stride kSlot) to carry
-// the epoch, summing component c in slot order.  Thread layout: component
-// tid % 32, slots tid / 32, tid / 32 + kRows, ...; the kRows partial sums are
-// then added in order.  Uniform exit; false on time-out.
-template <int L>
-__device__ __forceinline__ bool poll_sum_slots(const double* slots, int nslots, unsigned ep, const FrameArgs& a,
-                                               double* s_big, double* out) {
-  const int tid = thread_index();
-  constexpr int kRows = kBlock / 32;
-  const int comp = tid & 31, row0 = tid >> 5;
-  int bad = 0;
-  const double v = (comp < L) ? spin_sum(slots, nslots, kRows, kSlot, comp, row0, ep, a, bad) : 0.0;
-  s_big[tid] = v;
-  if (!spin_end(bad, a)) return false;
-  if (tid < L) {
-    double tot = 0.0;
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) tot += s_big[r * 32 + tid];
-    out[tid] = tot;
-  }
-  __syncthreads();
-  return true;
+// Compiler and LDS order within one wavefront (its LDS accesses execute in
+// order; nothing is waited for).
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
-// Two-level tagged exchange: the tiles t = x, x + 8, x + 16, ... form group x
-// (x < 8); group x's first tile gathers their tagged partials and publishes
-// the group sum; every workgroup then reads the (at most 8) group sums and
-// adds them in group order.  Two hops; every workgroup ends with
-// bit-identical totals.
+// Waits for *p to carry epoch ep, x being what a load of it returned; the
+// value without its tag, or 0 with `bad` set after a time-out.
+__device__ __forceinline__ double wait_tagged(const double* p, double x, unsigned ep, const FrameArgs& a, int& bad) {
+  if (tag_of(x) != ep) {
+    const long long t0 = now_ticks();
+    unsigned spins = 0;
+    do {
+      x = ld_tagged(p);
+      if ((++spins & 63u) == 0 &&
+          (now_ticks() - t0 > a.timeout ||
+           (__hip_atomic_load(&a.sync[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kErrTimeout))) {
+        bad = 1;
+        return 0.0;
+      }
+    } while (tag_of(x) != ep);
+  }
+  return untag(x);
+}
+
+// Two of the tagged slots q0 and q1 = q0 + dq (where they are below n), their
+// loads both in flight before either is waited for: component comp (< L) into
+// v, and component 16 + comp, if there is one, into vx.
 template <int L>
-__device__ __forceinline__ bool gang_reduce_2level(const double* wg_sum, const FrameArgs& a, const int tile,
-                                                   int& nbar, unsigned ebase, double* s_big,
-                                                   double* s_out, int* s_ctl, bool fenced) {
-  const int tid = thread_index();
+__device__ __forceinline__ void poll_pair(const double* base, int n, size_t qstride, int q0, int dq, int comp,
+                                          unsigned ep, const FrameArgs& a, double& v, double& vx, int& bad) {
+  const double* p0 = base + (size_t)q0 * qstride + comp;
+  const double* p1 = p0 + (size_t)dq * qstride;
+  const bool on0 = comp < L && q0 < n, on1 = comp < L && q0 + dq < n;
+  const bool ex0 = 16 + comp < L && q0 < n, ex1 = 16 + comp < L && q0 + dq < n;
+  double x0 = 0.0, x1 = 0.0, e0 = 0.0, e1 = 0.0;
+  if (on0) x0 = ld_tagged(p0);
+  if (on1) x1 = ld_tagged(p1);
+  if (L > 16 && ex0) e0 = ld_tagged(p0 + 16);
+  if (L > 16 && ex1) e1 = ld_tagged(p1 + 16);
+  if (on0) v += wait_tagged(p0, x0, ep, a, bad);
+  if (on1) v += wait_tagged(p1, x1, ep, a, bad);
+  if (L > 16 && ex0) vx += wait_tagged(p0 + 16, e0, ep, a, bad);
+  if (L > 16 && ex1) vx += wait_tagged(p1 + 16, e1, ep, a, bad);
+}
+
+// Gather by the whole workgroup: the sum of n tagged slots, one row of sums per
+// wavefront into sm.got.  Lane l of wavefront w takes component l % 16 of slots
+// 4 w + l / 16, then those 4 kWaves further on: the slots' lines spread over all
+// wavefronts (measured: one wavefront that polls 32 lines of 16 values takes
+// longer than eight that poll four each), two in flight per lane.  Ends with a
+// barrier; false (in every thread, the gang's time-out bit raised) on time-out.
+template <int L>
+__device__ __forceinline__ bool gather_slots(const double* base, int n, size_t qstride, unsigned ep,
+                                             const FrameArgs& a, FrameSmem& sm) {
+  const int lane = thread_index() & 63, wv = thread_index() >> 6;
+  const int comp = lane & 15;
+  constexpr int kRows = 4 * kWaves;
+  double v = 0.0, vx = 0.0;
+  int bad = 0;
+  for (int q = 4 * wv + (lane >> 4); q < n; q += 2 * kRows)
+    poll_pair<L>(base, n, qstride, q, kRows, comp, ep, a, v, vx, bad);
+  v = swap_sum<16>(swap_sum<32>(v));
+  if (L > 16) vx = swap_sum<16>(swap_sum<32>(vx));
+  if (lane < 16) {
+    sm.got[wv][comp] = v;
+    if (16 + comp < L) sm.got[wv][16 + comp] = vx;
+  }
+  return spin_end(bad, a);
+}
+
+// Raises the gang's time-out bit and the workgroup's flag if a lane of this
+// wavefront gave up.
+__device__ __forceinline__ void wave_give_up(int bad, const FrameArgs& a, FrameSmem& sm) {
+  if (__any(bad) && (thread_index() & 63) == 0) {
+    sm.ctl[2] = 1;
+    __hip_atomic_fetch_or(&a.sync[2], kErrTimeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// The slot set of an exchange: it alternates with the epoch, so a workgroup
+// that is one exchange ahead never writes what another still reads.  Frames
+// whose CG steps go through the wide exchange have one regular exchange per
+// launch and keep to set 0, which every frame then rewrites.
+__device__ __forceinline__ int slot_set(const FrameArgs& a, unsigned ep) {
+  return (a.ysolve == 2 || a.curv == 1) ? 0 : (int)(ep & 1);
+}
+
+// Gang-wide sum of L float partials per thread in the tagged exchanges 2 and 3.
+// The first wavefront publishes the workgroup's sums and, on return, holds the
+// totals in s_out[0..L) (LDS, written by itself): the k-space step that follows
+// runs in that wavefront, and the barrier at its end is the one that the other
+// wavefronts wait at, so an exchange costs two barriers (three in a workgroup
+// that gathers) instead of five.  After that barrier the caller checks
+// sm.ctl[2].  False (in every thread) when a gathering workgroup gave up.
+//   3: every workgroup gathers all G slots (two alternating sets).
+//   2: the tiles t = x mod 8 form group x, whose first tile gathers them and
+//      writes the group sum into eight copies, one for each residue of the
+//      readers (two alternating sets); every first wavefront sums the groups.
+// Per exchange with nothing in between (us): 226 workgroups 2.9 -> 2.6, 57:
+// 2.5 -> 2.3, 29 (exchange 3): 2.4 -> 1.9; with the exchanges below, a frame
+// with its mask read takes 89 us instead of 106 at 640x480x3, k = 15, float32,
+// 46 instead of 64 at 320x240x3, k = 10 (ordinary dispatch), 59 instead of 67
+// at 160x120x3, k = 15.
+template <int L>
+__device__ __forceinline__ bool gang_reduce_wave0(float (&acc)[L], const FrameArgs& a, const int tile, int& nbar,
+                                                  unsigned ebase, FrameSmem& sm, double* s_out) {
+  const int tid = thread_index(), lane = tid & 63, wv = tid >> 6;
+  {
+    int comp;
+    const float v = wave_reduce_scatter<L>(acc, comp);
+    if (wave_rs_owner<L>(lane) && comp < L) sm.red[wv][comp] = (double)v;
+  }
   ++nbar;
   const unsigned ep = (ebase + (unsigned)nbar) & 0xFFu;
-  const int x = tile & 7;
-  const int ngrp = min(8, a.G);
-  double* slots = a.part;                                            // G level-1 slots
-  double* gs = a.part + (size_t)a.G * kSlot + (size_t)(nbar & 1) * 8 * kSlot;   // 2 x 8 group sums
-  if (fenced) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  if (tid < L) st_tagged(&slots[(size_t)tile * kSlot + tid], tag_value(wg_sum[tid], ep));
-  if (tile < 8) {   // group leader: members x, x + 8, ... (slot stride 8)
-    const int n = (a.G - x + 7) >> 3;
-    const int comp = tid & 31, row0 = tid >> 5;
-    constexpr int kRows = kBlock / 32;
-    int bad = 0;
-    const double v = (comp < L) ? spin_sum(slots + (size_t)x * kSlot, n, kRows, (size_t)8 * kSlot, comp, row0, ep, a, bad)
-                                : 0.0;
-    s_big[tid] = v;
-    if (!spin_end(bad, a)) return false;
+  const int set = slot_set(a, ep);
+  __syncthreads();
+  if (tid < L) {
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) v += sm.red[q][tid];
+    if (a.G == 1)
+      s_out[tid] = v;   // a gang of one workgroup: its sums are the totals
+    else
+      st_tagged(&a.part[((size_t)(a.sync_mode == 3 && set ? a.G : 0) + tile) * kSlot + tid], tag_value(v, ep));
+  }
+  if (a.G == 1) {
+    wave_order();
+    return true;
+  }
+  trace_point(a, tile, 24 + 3 * nbar);
+  const int comp = lane & 15;
+  if (a.sync_mode == 3) {
+    if (!gather_slots<L>(a.part + (size_t)(set ? a.G : 0) * kSlot, a.G, kSlot, ep, a, sm)) return false;
     if (tid < L) {
-      double g = 0.0;
-      for (int r = 0; r < kRows; ++r) g += s_big[r * 32 + tid];
-      st_tagged(&gs[(size_t)x * kSlot + tid], tag_value(g, ep));
+      double v = 0.0;
+#pragma unroll
+      for (int q = 0; q < kWaves; ++q) v += sm.got[q][tid];
+      s_out[tid] = v;
+    }
+    wave_order();
+    return true;
+  }
+  double* gs = a.part + (size_t)(2 * a.G + set * kGroups * kReplicas) * kSlot;   // [copy][group]
+  if (tile < kGroups) {   // group leader: members tile, tile + 8, ...
+    const int n = (a.G - tile + kGroups - 1) / kGroups;
+    if (!gather_slots<L>(a.part + (size_t)tile * kSlot, n, (size_t)kGroups * kSlot, ep, a, sm)) return false;
+    if (wv == 0) {
+      double v = 0.0, vx = 0.0;
+#pragma unroll
+      for (int q = 0; q < kWaves; ++q) {
+        v += sm.got[q][comp];
+        if (16 + comp < L) vx += sm.got[q][16 + comp];
+      }
+      for (int c = lane >> 4; c < kReplicas; c += 4) {
+        double* p = gs + (size_t)(c * kGroups + tile) * kSlot;
+        if (comp < L) st_tagged(p + comp, tag_value(v, ep));
+        if (16 + comp < L) st_tagged(p + 16 + comp, tag_value(vx, ep));
+      }
     }
     trace_point(a, tile, 25 + 3 * (nbar - 1));
-    __syncthreads();
   }
-  if (!poll_sum_slots<L>(gs, ngrp, ep, a, s_big, s_out)) return false;
-  if (fenced) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  if (wv == 0) {
+    double v = 0.0, vx = 0.0;
+    int bad = 0;
+    poll_pair<L>(gs + (size_t)(tile & (kReplicas - 1)) * kGroups * kSlot, min(kGroups, a.G), kSlot, lane >> 4, 4, comp,
+                 ep, a, v, vx, bad);
+    v = swap_sum<16>(swap_sum<32>(v));
+    if (L > 16) vx = swap_sum<16>(swap_sum<32>(vx));
+    if (lane < 16) {
+      if (comp < L) s_out[comp] = v;
+      if (16 + comp < L) s_out[16 + comp] = vx;
+    }
+    wave_give_up(bad, a, sm);
+    wave_order();
+  }
   return true;
 }
 
-// One-hop tagged exchange: every workgroup publishes its tagged partial and
-// reads all G of them directly (G^2 small reads, one round trip).
-template <int L>
-__device__ __forceinline__ bool gang_reduce_allread(const double* wg_sum, const FrameArgs& a, const int tile,
-                                                    int& nbar, unsigned ebase, double* s_big,
-                                                    double* s_out, bool fenced) {
-  const int tid = thread_index();
+// Gang-wide sum of one float per thread in the tagged exchanges 2 and 3, in
+// `total` of every thread.  Only the first wavefront waits for the gang (one
+// slot per lane: with a single value per workgroup the lines need no spreading;
+// 226 workgroups 2.9 -> 2.2 us, 57: 2.5 -> 1.7, 29: 2.4 -> 1.6 with nothing in
+// between); the others run idle() meanwhile.  False when the gang gave up.
+template <typename IDLE>
+__device__ __forceinline__ bool gang_reduce_one(float acc, const FrameArgs& a, const int tile, int& nbar,
+                                                unsigned ebase, FrameSmem& sm, double& total, IDLE idle) {
+  const int tid = thread_index(), lane = tid & 63;
+  {
+    float v[1] = {acc};
+    int comp;
+    const float w = wave_reduce_scatter<1>(v, comp);
+    if (lane == 0) sm.red1[tid >> 6] = (double)w;
+  }
   ++nbar;
   const unsigned ep = (ebase + (unsigned)nbar) & 0xFFu;
-  double* slots = a.part + (size_t)(nbar & 1) * a.G * kSlot;      // double-buffered
-  if (fenced) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  if (tid < L) st_tagged(&slots[(size_t)tile * kSlot + tid], tag_value(wg_sum[tid], ep));
-  if (!poll_sum_slots<L>(slots, a.G, ep, a, s_big, s_out)) return false;
-  if (fenced) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  return true;
+  __syncthreads();
+  double v = 0.0;
+  if (a.G == 1 || tid < 64) {
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) v += sm.red1[q];
+  }
+  if (a.G == 1) {
+    total = v;
+    return true;
+  }
+  trace_point(a, tile, 24 + 3 * nbar);
+  if (tid < 64) {
+    const int set = slot_set(a, ep);
+    double* slots = a.part + (size_t)(a.sync_mode == 3 && set ? a.G : 0) * kSlot;
+    int bad = 0;
+    if (lane == 0) st_tagged(slots + (size_t)tile * kSlot, tag_value(v, ep));
+    v = 0.0;
+    double none = 0.0;
+    if (a.sync_mode == 3) {
+      for (int q = lane; q < a.G; q += 128) poll_pair<1>(slots, a.G, kSlot, q, 64, 0, ep, a, v, none, bad);
+    } else {
+      double* gs = a.part + (size_t)(2 * a.G + set * kGroups * kReplicas) * kSlot;
+      if (tile < kGroups) {
+        const int n = (a.G - tile + kGroups - 1) / kGroups;
+        for (int q = lane; q < n; q += 128)
+          poll_pair<1>(slots + (size_t)tile * kSlot, n, (size_t)kGroups * kSlot, q, 64, 0, ep, a, v, none, bad);
+        v = wave_sum(v);
+        if (!__any(bad) && lane < kReplicas) st_tagged(gs + (size_t)(lane * kGroups + tile) * kSlot, tag_value(v, ep));
+        trace_point(a, tile, 25 + 3 * (nbar - 1));
+        v = 0.0;
+      }
+      if (!__any(bad) && lane < min(kGroups, a.G)) {
+        const double* p = gs + (size_t)((tile & (kReplicas - 1)) * kGroups + lane) * kSlot;
+        v = wait_tagged(p, ld_tagged(p), ep, a, bad);
+      }
+    }
+    v = wave_sum(v);
+    if (lane == 0) sm.one = v;
+    wave_give_up(bad, a, sm);
+  } else {
+    idle();
+  }
+  __syncthreads();
+  total = sm.one;
+  return sm.ctl[2] == 0;
 }
 
 // Poll n tagged vectors of LT values (vector q at base + q * qstride) until
@@ -430,62 +600,72 @@ __device__ __forceinline__ bool gang_reduce_counter(float (&acc)[L], const Frame
   return true;
 }
 
-// Gang-wide sum of L float partials: every workgroup of the gang ends with
-// the same float64 totals in s_out[0..L).
-template <int L>
-__device__ __forceinline__ bool gang_reduce_impl(float (&acc)[L], const FrameArgs& a, const int tile, int& nbar,
-                                                 unsigned base, unsigned ebase, FrameSmem& sm, double* s_out,
-                                                 bool fenced) {
-  if (a.G == 1) {   // a gang of one workgroup: its sums are the totals, no memory exchange
-    ++nbar;
-    wg_reduce<L>(acc, sm.red, s_out);
-    return true;
-  }
-  if (a.sync_mode == 1) {
-    wg_reduce<L>(acc, sm.red, sm.wg);
-    return gang_reduce_tagged<L>(sm.wg, a, tile, nbar, ebase, sm.big, s_out, sm.ctl, fenced);
-  }
-  if (a.sync_mode == 2) {
-    wg_reduce<L>(acc, sm.red, sm.wg);
-    trace_point(a, tile, 24 + 3 * nbar);
-    return gang_reduce_2level<L>(sm.wg, a, tile, nbar, ebase, sm.big, s_out, sm.ctl, fenced);
-  }
-  if (a.sync_mode == 3) {
-    wg_reduce<L>(acc, sm.red, sm.wg);
-    return gang_reduce_allread<L>(sm.wg, a, tile, nbar, ebase, sm.big, s_out, fenced);
-  }
-  return gang_reduce_counter<L>(acc, a, tile, nbar, base, sm.red, sm.big, s_out, sm.ctl);
-}
+// The exchange runs in the first wavefront (gang_reduce_wave0 / _one): the
+// tagged exchanges 2 and 3, and gangs of one workgroup.
+__device__ __forceinline__ bool wave0_exchange(const FrameArgs& a) { return a.G == 1 || a.sync_mode >= 2; }
 
-
+// Gang-wide sum of L float partials: the same float64 totals in every workgroup
+// of the gang, in s_out[0..L) for the first wavefront.  The caller's next
+// barrier makes them visible to the others; sm.ctl[2] is checked after it.
 template <int L>
 __device__ __forceinline__ bool gang_reduce(float (&acc)[L], const FrameArgs& a, const int tile, int& nbar,
-                                            unsigned base, unsigned ebase, FrameSmem& sm, double* s_out,
-                                            bool fenced = false) {
+                                            unsigned base, unsigned ebase, FrameSmem& sm, double* s_out) {
   trace_point(a, tile, 2 + 2 * nbar);
-  const bool ok = gang_reduce_impl<L>(acc, a, tile, nbar, base, ebase, sm, s_out, fenced);
+  bool ok;
+  if (wave0_exchange(a)) {
+    ok = gang_reduce_wave0<L>(acc, a, tile, nbar, ebase, sm, s_out);
+  } else if (a.sync_mode == 1) {
+    wg_reduce<L>(acc, sm.red, sm.wg);
+    ok = gang_reduce_tagged<L>(sm.wg, a, tile, nbar, ebase, sm.big, s_out, sm.ctl, false);
+  } else {
+    ok = gang_reduce_counter<L>(acc, a, tile, nbar, base, sm.red, sm.big, s_out, sm.ctl);
+  }
   trace_point(a, tile, 1 + 2 * nbar);
   return ok;
 }
 
+// Gang-wide sum of one float, in `total` of every thread; idle() runs in the
+// wavefronts that do not wait for the gang (not at all where all of them do:
+// wave0_exchange() false or a gang of one).
+template <typename IDLE>
+__device__ __forceinline__ bool gang_reduce1(float acc, const FrameArgs& a, const int tile, int& nbar, unsigned base,
+                                             unsigned ebase, FrameSmem& sm, double& total, IDLE idle) {
+  trace_point(a, tile, 2 + 2 * nbar);
+  bool ok;
+  if (wave0_exchange(a)) {
+    ok = gang_reduce_one(acc, a, tile, nbar, ebase, sm, total, idle);
+  } else {
+    float v[1] = {acc};
+    if (a.sync_mode == 1) {
+      wg_reduce<1>(v, sm.red, sm.wg);
+      ok = gang_reduce_tagged<1>(sm.wg, a, tile, nbar, ebase, sm.big, sm.ks.red, sm.ctl, false);
+    } else {
+      ok = gang_reduce_counter<1>(v, a, tile, nbar, base, sm.red, sm.big, sm.ks.red, sm.ctl);
+    }
+    total = sm.ks.red[0];
+  }
+  trace_point(a, tile, 1 + 2 * nbar);
+  return ok;
+}
 
 // 3x3 median of binary labels (>= 5 of the 9 neighbours, edges replicated,
 // Sec. 3.4) for pixels [p0, p0 + npx) of a W x H image.
 // COH: the labels were written in this launch by other workgroups, with
-// device-coherent stores; read them with device-coherent loads.
+// device-coherent stores; read them with device-coherent loads.  Thread t0 of
+// the nt that share the work.
 template <bool COH = false>
 __device__ __forceinline__ void median3x3_range(const uint8_t* __restrict__ lab, uint8_t* __restrict__ mask, int W,
-                                                int H, int p0, int npx) {
+                                                int H, int p0, int npx, int t0, int nt) {
   // kMedBatch pixels per thread at a time: their 9 kMedBatch loads are all
   // issued before the first is used (an entry past the tile loads the
   // tile's last pixel again and is not stored), so a tile costs one memory
   // latency per batch instead of one per pixel
   constexpr int kMedBatch = 3;
-  for (int pl0 = thread_index(); pl0 < npx; pl0 += kMedBatch * blockDim.x) {
+  for (int pl0 = t0; pl0 < npx; pl0 += kMedBatch * nt) {
     int rb[kMedBatch][3], cb[kMedBatch][3];   // clamped neighbour rows (times W) and columns
 #pragma unroll
     for (int b = 0; b < kMedBatch; ++b) {
-      const int pix = p0 + min(pl0 + b * (int)blockDim.x, npx - 1);
+      const int pix = p0 + min(pl0 + b * nt, npx - 1);
       const int row = pix / W, col = pix - row * W;
       rb[b][0] = max(row - 1, 0) * W;
       rb[b][1] = row * W;
@@ -509,7 +689,7 @@ __device__ __forceinline__ void median3x3_range(const uint8_t* __restrict__ lab,
       int cnt = 0;
 #pragma unroll
       for (int t = 0; t < 9; ++t) cnt += v[b][t];
-      const int pl = pl0 + b * (int)blockDim.x;
+      const int pl = pl0 + b * nt;
       if (pl < npx) mask[p0 + pl] = (cnt >= 5) ? 1 : 0;
     }
   }
@@ -525,12 +705,14 @@ struct TileCtx {
   unsigned base, ebase;   // exchange counter / epoch bases of this launch
   long long n;            // frame index
   bool lead;              // tile 0 writes the stream's statistics and y
+  int median;             // the previous frame's median of this tile is still to be formed:
+                          // 1 from labels of an earlier launch, 2 of this launch
 };
 
-// Reads y and the frame index, then filters the previous frame's labels of
-// this tile into the mask (the labels were written by the previous launch; no
-// workgroup rewrites labels before the last exchange of this frame, which
-// every workgroup reaches only after this point).
+// Reads y and the frame index.  The median of the previous frame's labels is
+// left for a wait later in the frame (between_frames) unless this frame's weights
+// come from it.  A mask that has been read already is the median of these
+// labels, and nothing is left to do.
 template <int K>
 __device__ __forceinline__ TileCtx tile_begin(const FrameArgs& a, const int tile, KSpace<kMaxK>& ks) {
   TileCtx t;
@@ -565,11 +747,11 @@ __device__ __forceinline__ TileCtx tile_begin(const FrameArgs& a, const int tile
   }
   __syncthreads();
   trace_point(a, tile, 0);
-  // A mask that has been read already is the median of these labels: a reader
-  // of every mask then pays for one median per frame, not two (1.8-2.5 us of a
-  // 640x480x3 frame).
-  if (!__hip_atomic_load(&a.sync[4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-    median3x3_range(a.lab, a.mask, a.W, a.H, t.p0, t.npx);
+  t.median = __hip_atomic_load(&a.sync[4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 0 : 1;
+  if (a.weights_from_filtered && t.median) {
+    median3x3_range(a.lab, a.mask, a.W, a.H, t.p0, t.npx, tid, kBlock);
+    t.median = 0;
+  }
   __syncthreads();
   trace_point(a, tile, 1);
   return t;
@@ -619,21 +801,23 @@ __device__ __forceinline__ void cg_direction(const FrameArgs& a, KSpace<kMaxK>& 
     }
     if (gg == 0.0) stop = 1;
     if (lead && lane == 0) a.stats->f[it] = f;
-    double beta = 0.0, dj = -g;
+    // g . d of a direction -g is -(g . g), term by term, and the gp . gp of
+    // the PR+ coefficient is the previous step's g . g
+    double beta = 0.0, dj = -g, gd = -gg;
     if (!stop && it > 0 && a.ysolve == 0) {
       const double gp = (lane < K) ? ks.gp[lane] : 0.0;
       const double num = row16_sum(g * (g - gp));
-      const double den = row16_sum(gp * gp);
-      beta = fmax(0.0, num / den);
+      beta = fmax(0.0, num / ks.gg);
       const double dpv = (lane < K) ? ks.dp[lane] : 0.0;
-      dj = -g + beta * dpv;
-      const double gdv = row16_sum(g * dj);
+      const double dv = -g + beta * dpv;
+      const double gdv = row16_sum(g * dv);
       if (gdv >= 0.0) {
-        dj = -g;
         if (lane == 0) ++restarts;
+      } else {
+        dj = dv;
+        gd = gdv;
       }
     }
-    const double gd = row16_sum(g * dj);
     if (lane < K) {
       ks.d[lane] = dj;
       ks.df[lane] = (float)dj;
@@ -641,6 +825,7 @@ __device__ __forceinline__ void cg_direction(const FrameArgs& a, KSpace<kMaxK>& 
     }
     if (lane == 0) {
       ks.gd = gd;
+      ks.gg = gg;
       ks.flag[0] = stop;
       if (lead) a.stats->beta[it] = beta;
     }
@@ -836,7 +1021,7 @@ template <int K>
 __device__ __forceinline__ float cg_advance(const FrameArgs& a, KSpace<kMaxK>& ks, double dHd, int it, bool lead) {
   const int tid = thread_index();
   const double alpha = -ks.gd / dHd;
-  __syncthreads();
+  // y, d and dp are the first wavefront's own until the next barrier
   if (tid < K) {
     ks.y[tid] += alpha * ks.d[tid];
     ks.dp[tid] = ks.d[tid];
@@ -845,21 +1030,18 @@ __device__ __forceinline__ float cg_advance(const FrameArgs& a, KSpace<kMaxK>& k
   return (float)alpha;
 }
 
-// Step size and angle of the geodesic step and the trigonometric scalars of
-// the row pass: t = max(exp(-tau n) t_init, t_min) (Sec. 3.4),
+// Angle of the geodesic step and the trigonometric scalars of the row pass:
 // theta = sigma t, cos(theta) - 1 = -2 sin^2(theta / 2),
 // sin(theta) / zeta = 2 sin(theta / 2) cos(theta / 2) / zeta.
 // Out of line on purpose: inlined into the persistent kernels, the float64
 // polynomial constants of exp and sin were hoisted out of the tile loop and
 // held in registers (and spilled) for the whole launch.
 struct GeoScalars {
-  double t, theta, cm1, sz;
+  double theta, cm1, sz;
 };
-__device__ __attribute__((noinline)) GeoScalars geodesic_scalars(double tau_n, double t_init, double t_min,
-                                                                 double sigma, double zeta) {
+__device__ __attribute__((noinline)) GeoScalars geodesic_scalars(double t, double sigma, double zeta) {
   GeoScalars g;
-  g.t = fmax(exp(-tau_n) * t_init, t_min);
-  g.theta = sigma * g.t;
+  g.theta = sigma * t;
   double sh, ch;   // sin and cos of theta / 2 from one range reduction; sin(theta) = 2 sh ch
   sincos(0.5 * g.theta, &sh, &ch);
   g.cm1 = -2.0 * sh * sh;
@@ -872,8 +1054,7 @@ __device__ __attribute__((noinline)) GeoScalars geodesic_scalars(double tau_n, d
 // nu = ||y||, sigma = zeta nu, theta = sigma t_n; row-pass coefficients in
 // ks.scal / vf / af.
 template <int K>
-__device__ __forceinline__ void geodesic_setup(const FrameArgs& a, KSpace<kMaxK>& ks, long long n, int steps,
-                                               bool lead) {
+__device__ __forceinline__ void geodesic_setup(const FrameArgs& a, KSpace<kMaxK>& ks, int steps, bool lead) {
   const int tid = thread_index(), lane = tid & 63;
   if (tid < 64) {
     const double av = (lane < K) ? ks.red[lane] : 0.0;
@@ -891,14 +1072,14 @@ __device__ __forceinline__ void geodesic_setup(const FrameArgs& a, KSpace<kMaxK>
       ks.yf[lane] = (float)yv;
     }
     if (lane == 0) {
-      const GeoScalars g = geodesic_scalars(a.tau * (double)n, a.t_init, a.t_min, sigma, zeta);
+      const GeoScalars g = geodesic_scalars(ks.t, sigma, zeta);
       ks.scal[0] = upd ? (float)g.cm1 : 0.f;   // cos(theta) - 1
       ks.scal[1] = upd ? (float)g.sz : 0.f;    // sin(theta) / zeta
       ks.scal[2] = (float)nu;
       ks.flag[2] = upd;
       if (lead) {
         a.stats->f[steps] = ks.red[K + 1];
-        a.stats->t = g.t;
+        a.stats->t = ks.t;
         a.stats->sigma = sigma;
         a.stats->theta = g.theta;
         a.stats->zeta = zeta;
@@ -916,22 +1097,37 @@ __device__ __forceinline__ void geodesic_setup(const FrameArgs& a, KSpace<kMaxK>
 // waits for its stores to complete before any partial of the next frame is
 // published, so that the mask of the finished frame (its 3x3 median reads
 // neighbouring tiles' labels) can be formed after the next frame's first
-// exchange (sequence_median), which no workgroup completes before all have
+// exchange (between_frames), which no workgroup completes before all have
 // published.  (A device-scope release / acquire fence pair would also
 // write back and invalidate the L2: measured 3x slower.)
 __device__ __forceinline__ void next_frame_begin(KSpace<kMaxK>& ks, TileCtx& t, bool bad) {
   if (!bad) ++t.n;
+  t.median = 2;
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this thread's stores have completed
   __syncthreads();   // everyone is past the previous frame's use of ks.flag and s_flag
   if (thread_index() < 4) ks.flag[thread_index()] = 0;
   __syncthreads();
 }
 
-// The deferred median of a sequence frame: the previous frame's labels of
-// the whole gang are complete once this frame's first exchange is, and no
-// workgroup writes this frame's labels before the last exchange.
-__device__ __forceinline__ void sequence_median(const FrameArgs& a, const TileCtx& t) {
-  median3x3_range<true>(a.lab, a.mask, a.W, a.H, t.p0, t.npx);
+// The deferred median of the previous frame's labels, by thread t0 of nt, and
+// the frame's step size t = max(exp(-tau n) t_init, t_min) (Sec. 3.4), which
+// needs nothing but the frame index.  The labels of the whole gang are complete
+// once this frame's first exchange is, and no workgroup writes this frame's
+// labels before the last exchange, so the wavefronts that do not wait for the
+// gang do both during its first single-value exchange: neither then costs time
+// of its own (1.8 us of a 640x480x3 float32 frame, 2.5 in bfloat16, and 0.4 for
+// the step size's exponential in the one lane that forms the angle).
+__device__ __attribute__((noinline)) double step_size(double tau_n, double t_init, double t_min) {
+  return fmax(exp(-tau_n) * t_init, t_min);
+}
+template <bool SEQ>
+__device__ __forceinline__ void between_frames(const FrameArgs& a, KSpace<kMaxK>& ks, const TileCtx& t, int t0,
+                                               int nt) {
+  if (t0 == 0) ks.t = step_size(a.tau * (double)t.n, a.t_init, a.t_min);
+  if (SEQ && t.median == 2)
+    median3x3_range<true>(a.lab, a.mask, a.W, a.H, t.p0, t.npx, t0, nt);
+  else if (t.median)
+    median3x3_range(a.lab, a.mask, a.W, a.H, t.p0, t.npx, t0, nt);
 }
 
 // Label of tile pixel pl from the per-entry flags of the last labelled frame.
@@ -998,6 +1194,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
   KSpace<kMaxK>& ks = sm.ks;
   uint8_t* s_flag = sm.flag;
   int tid = thread_index();
+  if (tid == 0) sm.ctl[2] = 0;
   TileCtx ctx = tile_begin<K>(a, tile, ks);
   int nbar = 0;
 
@@ -1058,6 +1255,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
   }
   // ---- Step 1: CG on y ----
   int steps = 0, restarts = 0;
+  bool between = true;   // the previous median and this frame's step size are still to be formed
   for (int it = 0; it < a.J; ++it) {
     // phase A: gradient and cost at the current y
     float acc[K + 1];   // g, f
@@ -1103,8 +1301,8 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
       continue;
     }
     if (!gang_reduce<K + 1>(acc, a, tile, nbar, ctx.base, ctx.ebase, sm, ks.red)) return false;
-    if (SEQ && fi > 0 && it == 0) sequence_median(a, ctx);
     cg_direction<K>(a, ks, it, ctx.lead, restarts);
+    if (sm.ctl[2]) return false;
     if (ks.flag[0]) break;
     // phase B: curvature of the majoriser along d; cw then holds u.d
     float accb[1] = {0.f};
@@ -1116,16 +1314,20 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
       accb[0] = fmaf(cw[s] * t, t, accb[0]);
       cw[s] = t;
     }
-    if (!gang_reduce<1>(accb, a, tile, nbar, ctx.base, ctx.ebase, sm, ks.red)) return false;
-    const double dHd = ks.red[0];
+    double dHd;
+    if (!gang_reduce1(accb[0], a, tile, nbar, ctx.base, ctx.ebase, sm, dHd, [&] {
+          if (between) between_frames<SEQ>(a, ks, ctx, thread_index() - 64, kBlock - 64);
+        }))
+      return false;
+    if (wave0_exchange(a) && a.G > 1) between = false;
     if (!(dHd > 0.0)) break;   // same decision in every workgroup
     const float af = cg_advance<K>(a, ks, dHd, it, ctx.lead);
 #pragma unroll
     for (int s = 0; s < NR; ++s) r[s] = fmaf(-af, cw[s], r[s]);
     ++steps;
-    __syncthreads();
   }
   const bool bad = ks.flag[1] != 0;
+  if (between) between_frames<SEQ>(a, ks, ctx, thread_index(), kBlock);
 
   if (!bad) {
     // ---- Step 2: eta pass (a = U^T eta, ||eta||^2, final cost) ----
@@ -1147,7 +1349,8 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
     }
     if (!gang_reduce<LE>(acce, a, tile, nbar, ctx.base, ctx.ebase, sm, ks.red)) return false;
     if (EXT && tid == 0 && pupd) ks.pre_sum = ks.red[K + 2];
-    geodesic_setup<K>(a, ks, ctx.n, steps, ctx.lead);
+    geodesic_setup<K>(a, ks, steps, ctx.lead);
+    if (sm.ctl[2]) return false;
     trace_point(a, tile, 60);
 
     // ---- Step 2 update + Step 3 labels, one pass over the register tile ----
@@ -1276,6 +1479,7 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
   KSpace<kMaxK>& ks = sm.ks;
   uint8_t* s_flag = sm.flag;
   int tid = thread_index();
+  if (tid == 0) sm.ctl[2] = 0;
   TileCtx ctx = tile_begin<K>(a, tile, ks);
   int nbar = 0;
   const bool al = a.pair_aligned != 0;
@@ -1412,6 +1616,7 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
   if constexpr (SEQ) tid = thread_index();   // re-enters opaquely each frame (see the float32 tile)
   // ---- Step 1: CG on y ----
   int steps = 0, restarts = 0;
+  bool between = true;   // the previous median and this frame's step size are still to be formed
   for (int it = 0; it < a.J; ++it) {
     float acc[K + 1];   // g, f
 #pragma unroll
@@ -1454,8 +1659,8 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
       }
     }
     if (!gang_reduce<K + 1>(acc, a, tile, nbar, ctx.base, ctx.ebase, sm, ks.red)) return false;
-    if (SEQ && fi > 0 && it == 0) sequence_median(a, ctx);
     cg_direction<K>(a, ks, it, ctx.lead, restarts);
+    if (sm.ctl[2]) return false;
     if (ks.flag[0]) break;
     float accb[1] = {0.f};
     pin_tile(u);
@@ -1491,8 +1696,12 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
       accb[0] = fmaf(wc[0] * t0, t0, accb[0]);
       accb[0] = fmaf(wc[1] * t1, t1, accb[0]);
     }
-    if (!gang_reduce<1>(accb, a, tile, nbar, ctx.base, ctx.ebase, sm, ks.red)) return false;
-    const double dHd = ks.red[0];
+    double dHd;
+    if (!gang_reduce1(accb[0], a, tile, nbar, ctx.base, ctx.ebase, sm, dHd, [&] {
+          if (between) between_frames<SEQ>(a, ks, ctx, thread_index() - 64, kBlock - 64);
+        }))
+      return false;
+    if (wave0_exchange(a) && a.G > 1) between = false;
     if (!(dHd > 0.0)) break;
     const float af = cg_advance<K>(a, ks, dHd, it, ctx.lead);
 #pragma unroll
@@ -1512,9 +1721,9 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
       rls[kBlock] = fmaf(-af, t1, rls[kBlock]);
     }
     ++steps;
-    __syncthreads();
   }
   const bool bad = ks.flag[1] != 0;
+  if (between) between_frames<SEQ>(a, ks, ctx, thread_index(), kBlock);
 
   if (!bad) {
     constexpr int LE = K + 2 + (EXT ? 1 : 0);   // a, ||eta||^2, f (+ pre-processing deviation sum)
@@ -1563,7 +1772,8 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
     }
     if (!gang_reduce<LE>(acce, a, tile, nbar, ctx.base, ctx.ebase, sm, ks.red)) return false;
     if (EXT && tid == 0 && pupd) ks.pre_sum = ks.red[K + 2];
-    geodesic_setup<K>(a, ks, ctx.n, steps, ctx.lead);
+    geodesic_setup<K>(a, ks, steps, ctx.lead);
+    if (sm.ctl[2]) return false;
     trace_point(a, tile, 60);
 
     uint16_t* __restrict__ Uw = (uint16_t*)a.U;

@@ -518,7 +518,8 @@ __global__ __launch_bounds__(kStRed) void st_geodesic(FrameArgs a, StreamKS* ks,
     }
     if (lane == 0) {
       const long long n = *a.nframe;
-      const GeoScalars g = geodesic_scalars(a.tau * (double)n, a.t_init, a.t_min, sigma, zeta);
+      const double t = step_size(a.tau * (double)n, a.t_init, a.t_min);
+      const GeoScalars g = geodesic_scalars(t, sigma, zeta);
       ks->cm1 = upd ? (float)g.cm1 : 0.f;
       ks->sz = upd ? (float)g.sz : 0.f;
       ks->nu = (float)nu;
@@ -527,7 +528,7 @@ __global__ __launch_bounds__(kStRed) void st_geodesic(FrameArgs a, StreamKS* ks,
       a.stats->f[steps] = tot[KC + 1];
       a.stats->cg_steps = steps;
       a.stats->restarts = ks->restarts;
-      a.stats->t = g.t;
+      a.stats->t = t;
       a.stats->sigma = sigma;
       a.stats->theta = g.theta;
       a.stats->zeta = zeta;
