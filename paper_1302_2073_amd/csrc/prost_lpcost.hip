@@ -57,86 +57,131 @@ __device__ __forceinline__ void stage_rows(const float* __restrict__ U, long lon
   }
 }
 
-// Frames [b0, b0 + nb) of Y into LDS.
-template <int K, int CH>
-__device__ __forceinline__ void stage_frames(const float* __restrict__ Y, int b0, int nb, float (*ys)[K]) {
-  for (int q = thread_index(); q < nb * K; q += kLpBlock) ys[q / K][q % K] = Y[(long long)b0 * K + q];
+// Row block of this workgroup: consecutive blocks on one XCD (workgroups are
+// dealt to the 8 XCDs in turn).  The partial sums are laid out by output, one
+// float64 per block, so that the blocks of a 128-byte line then meet in one L2
+// instead of each writing 8 bytes of it to memory (27 MB of them in a backward
+// over 921600 rows, k = 15, 64 frames: 203 us without this order, 189 with it).
+__device__ __forceinline__ int lp_block() {
+  const int n = gridDim.x, x = blockIdx.x & 7, per = n >> 3, rem = n & 7;
+  return x * per + min(x, rem) + (int)(blockIdx.x >> 3);
 }
 
-// Frame entries of this thread's row for frames b .. b + kLpSub - 1 (0 past
-// the last frame or row): one coalesced load per frame across the workgroup.
-constexpr int kLpSub = 8;   // frames per prefetch step
-__device__ __forceinline__ void fetch_frames(float (&buf)[kLpSub], const float* __restrict__ X, long long m,
-                                             long long e, bool valid, int b, int B) {
+// One workgroup's entries of frame b of a (B, m) array as a buffer: row e0 + t at
+// byte 4 t.  The hardware's range check stands for both edges (rows past the
+// last one, frames past `frames`): a load there gives 0 without a memory access
+// and a store is dropped, so no lane takes a branch for its row.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t frame_rows(const float* X, long long m, long long e0, int nrow,
+                                                             int b, int frames) {
+  const bool in = b < frames;
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(X + (long long)(in ? b : 0) * m + e0), 0, in ? 4 * nrow : 0,
+                                           0x00027000);
+}
+
+// Frame entries of this thread's row for frames b .. b + kLpSub - 1 (0 past the
+// last frame or row): one coalesced load per frame across the workgroup.
+constexpr int kLpSub = 4;   // frames per prefetch step
+__device__ __forceinline__ void fetch_frames(float (&buf)[kLpSub], const float* X, long long m, long long e0, int nrow,
+                                             int b, int B, int off) {
 #pragma unroll
-  for (int i = 0; i < kLpSub; ++i) buf[i] = (valid && b + i < B) ? X[(long long)(b + i) * m + e] : 0.f;
+  for (int i = 0; i < kLpSub; ++i)
+    buf[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(frame_rows(X, m, e0, nrow, b + i, B), off, 0, 0));
 }
 
-// Forward: each thread owns one row e (u_e in registers) and walks the
-// frames in passes of kLpChunkF, eight at a time, with the next eight
-// frames' entries requested before the current ones are used (the loads of
-// the first eight are in flight while U and Y are staged), so memory and
-// arithmetic overlap within every workgroup.  Per frame the workgroup's sum
-// of w phi(r) is formed with one in-place reduce-scatter per pass and float64
-// across wavefronts.  Partials: part[b * nblk + workgroup].
+// Coefficients of frame b, the same for every lane: scalar loads.  As operands
+// read from LDS they took k reads per entry beside its k multiply-adds.
 template <int K>
+__device__ __forceinline__ void load_coeffs(float (&y)[K], const float* __restrict__ Y, int b) {
+#pragma unroll
+  for (int j = 0; j < K; ++j) y[j] = Y[(long long)b * K + j];
+}
+
+// The coefficients y are there: scalar loads return in any order, so a wait for
+// some is a wait for all, and the next frame's must not be asked for before
+// this frame's are in.
+template <int K>
+__device__ __forceinline__ void arrived(const float (&y)[K]) {
+#pragma unroll
+  for (int j = 0; j < K; ++j) asm volatile("" ::"s"(y[j]));
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Forward: each thread owns one row e (u_e in registers) and walks the frames in
+// passes of kLpChunkF, with the entries of the next step requested before the
+// current ones are used (the first are in flight while U is staged) and the
+// coefficients of two frames while the two before are worked on (two at a time:
+// with few wavefronts per SIMD the wait shows, 57600 rows, 15, 64: 19.6 us with
+// one, 16.4 with two).  A frame is a block
+// of its own behind a uniform branch: as one block the compiler asks for the
+// coefficients of all frames of a pass at once and spills scalar registers.
+// phi = exp2(p/2 log2 s) directly: two multiplications fewer than by way of c,
+// and a smaller exponent carries a smaller rounding error.  Per frame the
+// workgroup's sum of w phi(r) is formed with one in-place reduce-scatter per
+// pass and float64 across wavefronts.  Partials: part[b * nblk + block].
+// Bound by the reads of X (rows, k, frames: 921600, 15, 64: 130 us with
+// its finishing launch when y came from LDS, now 83, 3.6 TB/s; 230400, 10, 32:
+// 17.3, now 16.7).
+template <int K, int FORM>
 __global__ __launch_bounds__(kLpBlock) void lpcost_fwd_kernel(const float* __restrict__ U, const float* __restrict__ Y,
                                                               const float* __restrict__ X, const float* __restrict__ w,
-                                                              int m, int B, int form, float p, const float* __restrict__ mu_p,
+                                                              int m, int B, float p, const float* __restrict__ mu_p,
                                                               double* __restrict__ part) {
-  constexpr int CH = kLpChunkF;
-  constexpr int NS = CH / kLpSub;
+  constexpr int CH = kLpChunkF, NS = CH / kLpSub;
   __shared__ __align__(16) float uT[K][kLpPad];
-  __shared__ float ys[CH][K];
-  __shared__ double red[kLpWaves][CH];
-  // A run-time form here: with the form a compile-time constant the compiler
-  // hoists every frame's LDS reads of y ahead of the arithmetic and needs
-  // 256 VGPRs (one wavefront per SIMD, 2x slower); the backward gains from it.
-  const CostParams cp = make_cp(form, p, *mu_p);
+  __shared__ double red[2][kLpWaves][CH];
+  const CostParams cp = make_cp(FORM, p, *mu_p);
   const int tid = thread_index(), lane = tid & 63, wv = tid >> 6;
-  const int nblk = gridDim.x;
-  const long long e0 = (long long)blockIdx.x * kLpBlock;
+  const int nblk = gridDim.x, blk = lp_block();
+  const long long e0 = (long long)blk * kLpBlock;
   const int nrow = (int)((long long)m - e0 < kLpBlock ? (long long)m - e0 : kLpBlock);
-  const bool valid = tid < nrow;
-  const long long e = e0 + tid;
-  const float wt = valid ? (w ? w[e] : 1.0f) : 0.f;
+  const float wt = tid < nrow ? (w ? w[e0 + tid] : 1.0f) : 0.f;
   float xb[2][kLpSub];
-  fetch_frames(xb[0], X, m, e, valid, 0, B);
+  fetch_frames(xb[0], X, m, e0, nrow, 0, B, 4 * tid);
+  float y[4][K];   // frame b's in y[b & 3]
+  load_coeffs<K>(y[0], Y, 0);
+  load_coeffs<K>(y[1], Y, min(1, B - 1));
+  stage_rows<K>(U, e0, nrow, uT);
+  __syncthreads();
   float u[K];
-  for (int b0 = 0; b0 < B; b0 += CH) {
-    const int nb = min(CH, B - b0);
-    __syncthreads();
-    if (b0 == 0) stage_rows<K>(U, e0, nrow, uT);
-    stage_frames<K, CH>(Y, b0, nb, ys);
-    __syncthreads();
-    if (b0 == 0) {
 #pragma unroll
-      for (int j = 0; j < K; ++j) u[j] = uT[j][tid];
-    }
+  for (int j = 0; j < K; ++j) u[j] = uT[j][tid];
+  for (int b0 = 0, it = 0; b0 < B; b0 += CH, it ^= 1) {
+    const int nb = min(CH, B - b0);
     float acc[CH];
 #pragma unroll
     for (int st = 0; st < NS; ++st) {
-      fetch_frames(xb[(st + 1) & 1], X, m, e, valid, b0 + (st + 1) * kLpSub, B);   // the next eight
+      fetch_frames(xb[(st + 1) & 1], X, m, e0, nrow, b0 + (st + 1) * kLpSub, B, 4 * tid);
 #pragma unroll
       for (int i = 0; i < kLpSub; ++i) {
         const int bl = st * kLpSub + i;
-        float r = xb[st & 1][i];
+        acc[bl] = 0.f;
+        if (bl < nb) {   // uniform
+          if (bl % 2 == 0) {
+            arrived<K>(y[bl & 3]);
+            arrived<K>(y[(bl + 1) & 3]);
+            load_coeffs<K>(y[(bl + 2) & 3], Y, min(b0 + bl + 2, B - 1));
+            load_coeffs<K>(y[(bl + 3) & 3], Y, min(b0 + bl + 3, B - 1));
+            __builtin_amdgcn_sched_barrier(0);   // asked for before this frame's work, not after it
+          }
+          float r = xb[st & 1][i];
 #pragma unroll
-        for (int j = 0; j < K; ++j) r = fmaf(-u[j], ys[bl][j], r);
-        float phi, c;
-        cost_eval(r, cp, phi, c);
-        acc[bl] = (bl < nb) ? wt * phi : 0.f;
+          for (int j = 0; j < K; ++j) r = fmaf(-u[j], y[bl & 3][j], r);
+          if constexpr (FORM == 0)
+            acc[bl] = wt * __builtin_amdgcn_exp2f(cp.half_p * __builtin_amdgcn_logf(fmaf(r, r, cp.mu)));
+          else
+            acc[bl] = wt * (0.69314718055994531f * __builtin_amdgcn_logf(fmaf(r * r, cp.inv_mu, 1.0f)));
+        }
       }
     }
     int comp;
     const float v = wave_reduce_scatter<CH>(acc, comp);
-    if (wave_rs_owner<CH>(lane)) red[wv][comp] = (double)v;   // each component once per wavefront
-    __syncthreads();
+    if (wave_rs_owner<CH>(lane)) red[it][wv][comp] = (double)v;   // each component once per wavefront
+    __syncthreads();   // the other buffer's readers of two passes ago are past the barrier between
     if (tid < nb) {
       double sum = 0.0;
 #pragma unroll
-      for (int q = 0; q < kLpWaves; ++q) sum += red[q][tid];
-      part[(size_t)(b0 + tid) * nblk + blockIdx.x] = sum;
+      for (int q = 0; q < kLpWaves; ++q) sum += red[it][q][tid];
+      part[(size_t)(b0 + tid) * nblk + blk] = sum;
     }
   }
 }
@@ -144,99 +189,119 @@ __global__ __launch_bounds__(kLpBlock) void lpcost_fwd_kernel(const float* __res
 // Backward: per frame each thread forms s = g w phi'(r) for its row, writes
 // dX, accumulates its dU row and dmu in registers, and leaves s in LDS; after
 // each pass of kLpChunkB frames the workgroup's share of dY (pass x K) is
-// formed from LDS, one output per thread, rows in order.  Frame entries are
-// prefetched eight frames ahead as in the forward kernel.  Partials
-// (output q = b K + j of dY, then dmu at q = B K): part[q * nblk + workgroup].
+// formed from LDS on the matrix cores.  Frame entries and coefficients come as
+// in the forward kernel.  The rows of U are staged through the buffer that
+// holds s afterwards, once for the thread's own row and once as the matrix
+// operand, which stays in registers: half the LDS, written once per entry and
+// read 16 bytes at a time.  Bound by its reads and writes of X and dX
+// (rows, k, frames: 921600, 15, 64: 260 us with its finishing launch, now 182,
+// 3.4 TB/s; 230400, 10, 32: 27.1 and 28).  One frame's coefficients at a time:
+// two at a time spill scalar registers here.  Partials (output q = b K + j of dY,
+// then dmu at q = B K): part[q * nblk + block].
 template <int K, int FORM>
 __global__ __launch_bounds__(kLpBlock) void lpcost_bwd_kernel(const float* __restrict__ U, const float* __restrict__ Y,
                                                               const float* __restrict__ X, const float* __restrict__ w,
                                                               int m, int B, float p, const float* __restrict__ mu_p,
                                                               const float* __restrict__ gout, float* __restrict__ dX,
                                                               float* __restrict__ dU, double* __restrict__ part) {
-  constexpr int CH = kLpChunkB;
-  constexpr int NS = CH / kLpSub;
-  __shared__ __align__(16) float uT[K][kLpPad];
-  __shared__ __align__(16) float sdl[CH][kLpPad];
-  __shared__ float ys[CH][K];
-  __shared__ float gs[CH];
+  constexpr int CH = kLpChunkB, NS = CH / kLpSub;
+  __shared__ __align__(16) float sdl[CH][kLpPad];   // rows of U first, then s [frame][row], dU rows at the end
   __shared__ double redm[kLpWaves];
-  __shared__ double dyw[kLpWaves][16][17];   // per-wavefront dY tiles [frame][j]
+  __shared__ float dyw[kLpWaves][16][17];   // per-wavefront dY tiles [frame][j]
   static_assert(CH == 16 && K <= 16 && kLpBlock == 64 * kLpWaves, "one 16 x 16 tile per wavefront");
   const CostParams cp = make_cp(FORM, p, *mu_p);   // the form is a compile-time constant: no per-entry branch
   const int tid = thread_index(), lane = tid & 63, wv = tid >> 6;
-  const int nblk = gridDim.x;
-  const long long e0 = (long long)blockIdx.x * kLpBlock;
+  const int i16 = lane & 15, k4 = lane >> 4;
+  const int nblk = gridDim.x, blk = lp_block();
+  const long long e0 = (long long)blk * kLpBlock;
   const int nrow = (int)((long long)m - e0 < kLpBlock ? (long long)m - e0 : kLpBlock);
   const bool valid = tid < nrow;
-  const long long e = e0 + tid;
-  const float wt = valid ? (w ? w[e] : 1.0f) : 0.f;
+  const int nx = dX ? B : 0;   // frames of dX to store
+  const float wt = valid ? (w ? w[e0 + tid] : 1.0f) : 0.f;
   float u[K], du[K];
 #pragma unroll
   for (int j = 0; j < K; ++j) du[j] = 0.f;
   float dmu = 0.f;
   float xb[2][kLpSub];
-  fetch_frames(xb[0], X, m, e, valid, 0, B);
+  fetch_frames(xb[0], X, m, e0, nrow, 0, B, 4 * tid);
+  float y[2][K];   // frame b's in y[b & 1]
+  load_coeffs<K>(y[0], Y, 0);
+  float g[2] = {gout[0], 0.f};
+  stage_rows<K>(U, e0, nrow, sdl);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < K; ++j) u[j] = sdl[j][tid];
+  // matrix operand: column i16 of rows 16 k4 .. + 15 of this wavefront's 64
+  const int mrow = wv * 64 + k4 * 16;
+  float ub[16];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const float4 q = *(const float4*)&sdl[i16 < K ? i16 : 0][mrow + 4 * c];
+    ub[4 * c] = i16 < K ? q.x : 0.f;
+    ub[4 * c + 1] = i16 < K ? q.y : 0.f;
+    ub[4 * c + 2] = i16 < K ? q.z : 0.f;
+    ub[4 * c + 3] = i16 < K ? q.w : 0.f;
+  }
+  __syncthreads();
   for (int b0 = 0; b0 < B; b0 += CH) {
     const int nb = min(CH, B - b0);
-    __syncthreads();
-    if (b0 == 0) stage_rows<K>(U, e0, nrow, uT);
-    stage_frames<K, CH>(Y, b0, nb, ys);
-    if (tid < nb) gs[tid] = gout[b0 + tid];
-    __syncthreads();
-    if (b0 == 0) {
-#pragma unroll
-      for (int j = 0; j < K; ++j) u[j] = uT[j][tid];
-    }
 #pragma unroll
     for (int st = 0; st < NS; ++st) {
-      fetch_frames(xb[(st + 1) & 1], X, m, e, valid, b0 + (st + 1) * kLpSub, B);   // the next eight
+      fetch_frames(xb[(st + 1) & 1], X, m, e0, nrow, b0 + (st + 1) * kLpSub, B, 4 * tid);
 #pragma unroll
       for (int i = 0; i < kLpSub; ++i) {
         const int bl = st * kLpSub + i;
-        float sd = 0.f;
-        if (bl < nb && valid) {
+        if (bl < nb) {   // uniform
+          arrived<K>(y[bl & 1]);
+          const int next = min(b0 + bl + 1, B - 1);
+          load_coeffs<K>(y[(bl + 1) & 1], Y, next);
+          g[(bl + 1) & 1] = gout[next];
+          __builtin_amdgcn_sched_barrier(0);   // asked for before this frame's work, not after it
+          const __amdgpu_buffer_rsrc_t rows = frame_rows(dX, m, e0, nrow, b0 + bl, nx);
           float r = xb[st & 1][i];
 #pragma unroll
-          for (int j = 0; j < K; ++j) r = fmaf(-u[j], ys[bl][j], r);
+          for (int j = 0; j < K; ++j) r = fmaf(-u[j], y[bl & 1][j], r);
+          r = valid ? r : 0.f;                         // s = 0 past the last row, whatever y and g are
           float phi, c;
           cost_eval(r, cp, phi, c);
-          const float gw = gs[bl] * wt;
-          sd = gw * c * r;                         // g w phi'(r)
-          if (dX) dX[(long long)(b0 + bl) * m + e] = sd;
+          const float gw = valid ? g[bl & 1] * wt : 0.f;
+          const float sd = gw * c * r;                 // g w phi'(r)
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sd), rows, 4 * tid, 0, 0);
           dmu = fmaf(gw, dphi_dmu(r, c, cp), dmu);
 #pragma unroll
-          for (int j = 0; j < K; ++j) du[j] = fmaf(-sd, ys[bl][j], du[j]);
+          for (int j = 0; j < K; ++j) du[j] = fmaf(-sd, y[bl & 1][j], du[j]);
+          sdl[bl][tid] = sd;
         }
-        sdl[bl][tid] = sd;   // 0 past the last frame or row
       }
     }
     __syncthreads();
     // dY share of this workgroup: -sum_rows s[b][row] u[row][j], a 16 x 256
     // by 256 x K product on the matrix cores: wavefront w multiplies its 64
     // rows in 16 steps of v_mfma_f32_16x16x4f32 (A = s[frame][4 rows], B =
-    // u[4 rows][j], float32 accumulation), and the four wavefronts' 16 x 16
-    // tiles are added in order in float64.  Frames past nb and columns past
-    // K only reach outputs that are not written.
+    // u[4 rows][j], float32 accumulation; step st takes row st of each lane
+    // group's 16), and the four wavefronts' 16 x 16 tiles are added in order
+    // in float64.  Frames past nb and columns past K only reach outputs that
+    // are not written.
     {
-      const int i16 = lane & 15, k4 = lane >> 4;
       f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int st = 0; st < 16; ++st) {
-        const int row = wv * 64 + st * 4 + k4;
-        const float av = sdl[i16][row];
-        const float bv = (i16 < K) ? uT[i16 < K ? i16 : 0][row] : 0.f;
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc, 0, 0, 0);
+      for (int c = 0; c < 4; ++c) {
+        const float4 q = *(const float4*)&sdl[i16][mrow + 4 * c];
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(q.x, ub[4 * c], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(q.y, ub[4 * c + 1], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(q.z, ub[4 * c + 2], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(q.w, ub[4 * c + 3], acc, 0, 0, 0);
       }
 #pragma unroll
-      for (int v = 0; v < 4; ++v) dyw[wv][k4 * 4 + v][i16] = (double)acc[v];   // D[frame][j]
+      for (int v = 0; v < 4; ++v) dyw[wv][k4 * 4 + v][i16] = acc[v];   // D[frame][j]
     }
     __syncthreads();
     for (int q = tid; q < nb * K; q += kLpBlock) {
       const int bl = q / K, j = q - bl * K;
       double sum = 0.0;
 #pragma unroll
-      for (int w2 = 0; w2 < kLpWaves; ++w2) sum += dyw[w2][bl][j];
-      part[(size_t)((size_t)b0 * K + q) * nblk + blockIdx.x] = -sum;
+      for (int w2 = 0; w2 < kLpWaves; ++w2) sum += (double)dyw[w2][bl][j];
+      part[(size_t)((size_t)b0 * K + q) * nblk + blk] = -sum;
     }
   }
   if (dU) {   // coalesced store of the workgroup's dU rows through LDS
@@ -254,7 +319,7 @@ __global__ __launch_bounds__(kLpBlock) void lpcost_bwd_kernel(const float* __res
   if (tid == 0) {
     double v = 0.0;
     for (int q = 0; q < kLpWaves; ++q) v += redm[q];
-    part[(size_t)B * K * nblk + blockIdx.x] = v;
+    part[(size_t)B * K * nblk + blk] = v;
   }
 }
 
@@ -357,8 +422,12 @@ pros_status pros_lpcost_fwd(const float* U, const float* Y, const float* X, cons
   double* part = (double*)workspace;
   const int nblk = lp_blocks(m);
   const int form = (cost == PROS_COST_LOG) ? 1 : 0;
-  PROST_K_SWITCH(k, hipLaunchKernelGGL((lpcost_fwd_kernel<KK>), dim3(nblk), dim3(kLpBlock), 0, s, U, Y, X, w, m, B,
-                                       form, p, mu, part));
+  if (form)
+    PROST_K_SWITCH(k, hipLaunchKernelGGL((lpcost_fwd_kernel<KK, 1>), dim3(nblk), dim3(kLpBlock), 0, s, U, Y, X, w, m,
+                                         B, p, mu, part))
+  else
+    PROST_K_SWITCH(k, hipLaunchKernelGGL((lpcost_fwd_kernel<KK, 0>), dim3(nblk), dim3(kLpBlock), 0, s, U, Y, X, w, m,
+                                         B, p, mu, part))
   hipLaunchKernelGGL(lpcost_finish, dim3(B), dim3(256), 0, s, (const double*)part, nblk, B, B, f, (float*)nullptr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return prost_host::set_error(PROS_EHIP, "lpcost forward launch: %s", hipGetErrorString(e));
