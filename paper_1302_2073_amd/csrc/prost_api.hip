@@ -96,7 +96,9 @@ struct MaskJob {
   pros_stats* stats;
   unsigned char* header;  // pinned: error bits and statistics as they are after this launch; NULL: not wanted
 };
-constexpr int kMaskBlock = 256, kMaskPix = 4 * kMaskBlock;
+// The atomics meet on one address, about 10 ns each: at most kMaskGrid workgroups
+// (1280x720: 900 workgroups 13 us, 256 7.8 us).
+constexpr int kMaskBlock = 256, kMaskPix = 4 * kMaskBlock, kMaskGrid = 256;
 static_assert(sizeof(pros_stats) % 4 == 0 && sizeof(pros_stats) + 16 <= prost_host::kPinHeader &&
                   sizeof(pros_stats) / 4 <= kMaskBlock,
               "pinned header");
@@ -111,65 +113,73 @@ __device__ __forceinline__ void mask_header(const MaskJob& a, long long fg) {
   if (t == 0) *(uint32_t*)a.header = a.sync[2];
 }
 
+// Four pixels from p (np of them): their mask bytes in m, foreground labels
+// returned.
+__device__ __forceinline__ unsigned mask_quad(const MaskJob& a, int p, int np, uint32_t& m) {
+  m = 0;
+  if ((a.W & 3) == 0) {   // P is a multiple of 4 too: four pixels of one row, words aligned
+    const int row = p / a.W, col = p - row * a.W;
+    const int rb[3] = {max(row - 1, 0) * a.W, row * a.W, min(row + 1, a.H - 1) * a.W};
+    const int cl = max(col - 1, 0), cr = min(col + 4, a.W - 1);
+    uint32_t w[3], l[3], r[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      w[i] = *(const uint32_t*)(a.lab + rb[i] + col);
+      l[i] = a.lab[rb[i] + cl];
+      r[i] = a.lab[rb[i] + cr];
+    }
+    const uint32_t v = w[0] + w[1] + w[2];                       // column sums of the four pixels, a byte each
+    const uint32_t left = (v << 8) | (l[0] + l[1] + l[2]);       // of the columns one to the left
+    const uint32_t right = (v >> 8) | ((r[0] + r[1] + r[2]) << 24);
+    m = ((v + left + right + 0x7B7B7B7Bu) >> 7) & 0x01010101u;   // at least 5 of 9
+    return __popc(w[1]);
+  }
+  unsigned fg = 0;
+  for (int i = 0; i < np; ++i) {
+    const int row = (p + i) / a.W, col = (p + i) - row * a.W;
+    unsigned s = 0;
+    for (int dy = -1; dy <= 1; ++dy)
+      for (int dx = -1; dx <= 1; ++dx)
+        s += a.lab[min(max(row + dy, 0), a.H - 1) * a.W + min(max(col + dx, 0), a.W - 1)];
+    m |= (s >= 5 ? 1u : 0u) << (8 * i);
+    fg += a.lab[p + i];
+  }
+  return fg;
+}
+
+__device__ __forceinline__ void mask_store(uint8_t* to, int p, int np, uint32_t m) {
+  if (np == 4 && ((uintptr_t)to & 3u) == 0)
+    *(uint32_t*)(to + p) = m;
+  else
+    for (int i = 0; i < np; ++i) to[p + i] = (uint8_t)(m >> (8 * i));
+}
+
 __global__ __launch_bounds__(kMaskBlock) void mask_kernel(MaskJob a) {
   __shared__ unsigned cnt;
   __shared__ long long total;
-  const int p = (blockIdx.x * kMaskBlock + threadIdx.x) * 4;
-  if (a.src) {
-    if (p + 4 <= a.P && (((uintptr_t)a.out | (uintptr_t)a.src) & 3u) == 0)
-      *(uint32_t*)(a.out + p) = *(const uint32_t*)(a.src + p);
-    else
-      for (int q = p; q < min(p + 4, a.P); ++q) a.out[q] = a.src[q];
-    if (a.header && blockIdx.x == 0) mask_header(a, -1);
-    return;
-  }
   if (threadIdx.x == 0) {
     cnt = 0;
     total = -1;
   }
   __syncthreads();
   unsigned fg = 0;
-  if (p < a.P) {
-    uint32_t m = 0;
+  for (int p = (blockIdx.x * kMaskBlock + threadIdx.x) * 4; p < a.P; p += gridDim.x * kMaskPix) {
     const int np = min(4, a.P - p);
-    if ((a.W & 3) == 0) {   // P is a multiple of 4 too: four pixels of one row, words aligned
-      const int row = p / a.W, col = p - row * a.W;
-      const int rb[3] = {max(row - 1, 0) * a.W, row * a.W, min(row + 1, a.H - 1) * a.W};
-      const int cl = max(col - 1, 0), cr = min(col + 4, a.W - 1);
-      uint32_t w[3], l[3], r[3];
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        w[i] = *(const uint32_t*)(a.lab + rb[i] + col);
-        l[i] = a.lab[rb[i] + cl];
-        r[i] = a.lab[rb[i] + cr];
-      }
-      fg = __popc(w[1]);
-      const uint32_t v = w[0] + w[1] + w[2];                       // column sums of the four pixels, a byte each
-      const uint32_t left = (v << 8) | (l[0] + l[1] + l[2]);       // of the columns one to the left
-      const uint32_t right = (v >> 8) | ((r[0] + r[1] + r[2]) << 24);
-      m = ((v + left + right + 0x7B7B7B7Bu) >> 7) & 0x01010101u;   // at least 5 of 9
-    } else {
-      for (int i = 0; i < np; ++i) {
-        const int row = (p + i) / a.W, col = (p + i) - row * a.W;
-        unsigned s = 0;
-        for (int dy = -1; dy <= 1; ++dy)
-          for (int dx = -1; dx <= 1; ++dx)
-            s += a.lab[min(max(row + dy, 0), a.H - 1) * a.W + min(max(col + dx, 0), a.W - 1)];
-        m |= (s >= 5 ? 1u : 0u) << (8 * i);
-        fg += a.lab[p + i];
-      }
-    }
-    if (np == 4) {
-      *(uint32_t*)(a.mask + p) = m;
-    } else {
-      for (int i = 0; i < np; ++i) a.mask[p + i] = (uint8_t)(m >> (8 * i));
-    }
-    if (a.out) {
-      if (np == 4 && ((uintptr_t)a.out & 3u) == 0)
-        *(uint32_t*)(a.out + p) = m;
+    if (a.src) {
+      if (np == 4 && ((uintptr_t)a.src & 3u) == 0)
+        mask_store(a.out, p, 4, *(const uint32_t*)(a.src + p));
       else
-        for (int i = 0; i < np; ++i) a.out[p + i] = (uint8_t)(m >> (8 * i));
+        for (int i = 0; i < np; ++i) a.out[p + i] = a.src[p + i];
+      continue;
     }
+    uint32_t m;
+    fg += mask_quad(a, p, np, m);
+    mask_store(a.mask, p, np, m);
+    if (a.out) mask_store(a.out, p, np, m);
+  }
+  if (a.src) {
+    if (a.header && blockIdx.x == 0) mask_header(a, -1);
+    return;
   }
   if (fg) atomicAdd(&cnt, fg);
   __syncthreads();
@@ -191,7 +201,7 @@ __global__ __launch_bounds__(kMaskBlock) void mask_kernel(MaskJob a) {
 static pros_status launch_mask(pros_handle* h, const uint8_t* src, uint8_t* out, bool header, int np) {
   MaskJob j{h->lab, h->mask, out, src, h->prm.width, h->prm.height, np, h->sync, h->stats,
             header ? h->pin : nullptr};
-  hipLaunchKernelGGL(mask_kernel, dim3(std::max(1, (np + kMaskPix - 1) / kMaskPix)), dim3(kMaskBlock), 0, h->stream,
+  hipLaunchKernelGGL(mask_kernel, dim3(std::max(1, std::min(kMaskGrid, (np + kMaskPix - 1) / kMaskPix))), dim3(kMaskBlock), 0, h->stream,
                      j);
   HIP_TRY(hipGetLastError());
   return PROS_OK;
