@@ -499,8 +499,9 @@ PROS_API pros_status pros_batch_set_dispatch(pros_batch* b, int32_t cooperative)
  * float32 storage (PROS_EUNSUPPORTED otherwise) and a tagged exchange
  * (sync_mode 1..3).  The IRLS solver (ysolve = 2) always reduces H.
  * Synchronises; the tile (rows per thread) is kept.  On a streamed handle
- * (frames beyond the resident tiles) both schedules are available in either
- * storage type: schedule 1 reads U once per CG step instead of twice. */
+ * (frames beyond the resident tiles) both schedules are accepted in either
+ * storage type and run the same pass, which reads U once per CG step and forms
+ * H on the matrix cores beside the gradient. */
 PROS_API pros_status pros_set_curvature(pros_handle* h, int32_t schedule);
 
 /* ---------------------------------------------------------------------------

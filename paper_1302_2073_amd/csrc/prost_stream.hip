@@ -1,22 +1,30 @@
 // Frames too large for a resident gang of register tiles (Sec. 3.3, Steps
 // 1-3, with the step-size rule of Sec. 3.4): the same per-frame arithmetic as
 // the frame kernel, but every dependent pass streams U and the frame from
-// HBM, one launch per pass, with the k-space work between passes in one
-// small workgroup.  Per frame and CG step (Step 1):
-//   grad pass:   r = x - U y, phi, c; w c stored per entry; partials of
-//                U^T (w phi'(r)) and sum w phi(r)
-//   direction:   fixed-order sum of the partials, PR+ direction d
-//   curvature:   partials of sum w c (u . d)^2 (the majoriser's d^T H d)
-//   advance:     alpha = -g.d / d^T H d, y += alpha d
-// (curvature schedule 1 instead: one pass reduces g, f and the upper
-// triangle of H = U^T diag(w c) U, and one kernel forms d, d^T H d and the
-// step), then (Step 2) the eta pass (eta = -w phi'(r) stored per entry,
-// partials of U^T eta, ||eta||^2 and the final cost), the geodesic scalars,
-// and one pass that updates U and labels every pixel (Step 3).  A thread
-// takes one pixel (all channels), or two adjacent ones in bfloat16 storage
-// with even P and aligned planes (32-bit accesses).  Reductions: float32 per
-// thread, float64 per workgroup and across workgroups in a fixed order, so
-// results are deterministic.
+// HBM.  Per frame and CG step (Step 1):
+//   gradient pass: r = x - U y, phi, c; partials of U^T (w phi'(r)),
+//                  sum w phi(r) and the upper triangle of
+//                  H = U^T diag(w c) U
+//   step:          fixed-order sums of the partials, PR+ direction d,
+//                  d^T H d, alpha = -g.d / d^T H d, y += alpha d
+// then (Step 2) the eta pass (eta = -w phi'(r) stored per entry, partials of
+// U^T eta, ||eta||^2 and the final cost), the geodesic scalars, and one pass
+// that updates U and labels every pixel (Step 3).  A thread takes one pixel
+// (all channels), or two adjacent ones in bfloat16 storage with even P and
+// aligned planes (32-bit accesses).  Reductions: float32 per thread, float64
+// per workgroup and across workgroups in a fixed order, so results are
+// deterministic.
+//
+// A pass is bound by its reads, so a step reads U once: H (a contraction over
+// the rows with both operands U) is formed on the matrix cores in the shadow of
+// the read, where a second pass for sum w c (u.d)^2 took 26 us of a 1280x720x3,
+// k = 15 float32 step and k (k + 1) / 2 products per entry in the vector unit 38.
+// The sums of a step's partials run one workgroup per value, and the last of
+// them to finish takes the k-space step: two launches per CG step instead of
+// four, and none around the frame.  A 1280x720x3, k = 15 frame takes 307 us in
+// float32 (479 with the two-pass step) and 254 in bfloat16 (309); its gradient
+// pass 34.5 us, 5.1 TB/s, and 33, where the vector and matrix work no longer
+// hides behind half the bytes.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,12 +38,21 @@ namespace prost {
 
 constexpr int kStBlock = 256;           // threads per workgroup of a pass (one pixel or pixel pair each)
 constexpr int kStWaves = kStBlock / 64;
-constexpr int kStRed = 1024;            // threads of the reducing (k-space) kernels
-constexpr int kStL = kMaxK + 2;         // partials per workgroup: up to K values and two scalars
-constexpr int kStWide = 160;            // schedule 1: g (K), f and H's upper triangle (<= 153 values)
+constexpr int kStWide = 160;            // values of a gradient pass: g (K), f and H's upper triangle (<= 153)
 template <int KC>
 constexpr int st_nh() { return KC + 1 + KC * (KC + 1) / 2; }
-static_assert(st_nh<kMaxK>() <= kStWide, "wide partial vector");
+static_assert(st_nh<kMaxK>() <= kStWide && kStWide <= kStBlock, "one thread per value");
+constexpr int kStPad = 68;              // floats per column of a wavefront's 64 rows in LDS (16-byte aligned, spreads banks)
+
+// Workgroups of a reducing pass over nchunk groups of kStBlock threads' pixels:
+// five per compute unit, what both storage types hold at once, each taking
+// groups kStResident apart.  A pass leaves 1280 partials per value of a
+// 1280x720 frame instead of 3600 to sum, and every compute unit gets the same
+// share (a frame, float32 / bfloat16: 307 / 254 us; the same number of groups
+// for each workgroup, 1200 and 900 of them: 305 / 264; 1920x1080: 718 against
+// 750 in float32).
+constexpr int kStResident = 1280;
+static int st_blocks(int nchunk) { return std::min(nchunk, kStResident); }
 
 // k-space state of the frame being streamed (device memory, one per handle).
 struct StreamKS {
@@ -45,66 +62,37 @@ struct StreamKS {
   float df[kMaxK], vf[kMaxK], af[kMaxK];
   float cm1, sz, nu;
   int stop, bad, upd, steps, restarts;
-  double htot[kStWide];   // curvature schedule 1: reduced g, f and upper triangle of H
+  unsigned ticket;        // workgroups of a summing launch that are done
+  double tot[kStWide];    // reduced values of the latest pass
 };
 
-// Workgroup sum of L float partials per thread into part[blk * kStL + q]
-// (float64; fixed order: wavefront reduce-scatter, then wavefronts in order).
-template <int L>
-__device__ __forceinline__ void st_block_partials(float (&acc)[L], double (*red)[kStL], double* __restrict__ part) {
-  const int tid = thread_index(), lane = tid & 63, wv = tid >> 6;
-  int comp;
-  const float v = wave_reduce_scatter<L>(acc, comp);
-  if (wave_rs_owner<L>(lane) && comp < L) red[wv][comp] = (double)v;
-  __syncthreads();
-  if (tid < L) {
-    double s = 0.0;
-#pragma unroll
-    for (int w = 0; w < kStWaves; ++w) s += red[w][tid];
-    part[(size_t)blockIdx.x * kStL + tid] = s;
-  }
-}
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-// Sum over the nblk workgroups' partials of the first L values, into out[]
-// (shared).  Each value is summed by NG = kStRed / Lp threads (Lp: L rounded
-// up to a power of two): thread (q, g) takes workgroups g, g + NG, g + 2 NG,
-// ... in order (kStUnroll loads in flight), then the NG group sums are
-// folded in a fixed tree (the upper half onto the lower, down to 32) and
-// those are added in order.  Every step is fixed, so the result is
-// deterministic.
-constexpr int kStUnroll = 16;
-template <int L>
-__device__ __forceinline__ void st_sum_partials(const double* __restrict__ part, int nblk, double* grp,
-                                                double* out) {
-  constexpr int Lp = pow2_at_least(L);
-  constexpr int NG = kStRed / Lp;
-  static_assert(NG >= 32, "at least 32 threads per value");
-  const int t = threadIdx.x, q = t % Lp, g = t / Lp;
+// One value per workgroup of a summing launch: value v = blockIdx.x's partials
+// of the nblk workgroups of a pass (contiguous) in a fixed order, to ks->tot.
+// True in the workgroup that finishes last, which then sees all totals: they
+// go out as device-coherent stores, complete before the ticket is taken.
+__device__ __forceinline__ bool st_sum_value(StreamKS* ks, const double* __restrict__ part, int nblk, double* red,
+                                             int* last, double* tot) {
+  const int v = blockIdx.x, t = threadIdx.x;
+  const double* row = part + (size_t)v * nblk;
   double s = 0.0;
-  if (q < L) {
-    int b = g;
-    for (; b + (kStUnroll - 1) * NG < nblk; b += kStUnroll * NG) {
-      double v[kStUnroll];
-#pragma unroll
-      for (int i = 0; i < kStUnroll; ++i) v[i] = part[(size_t)(b + i * NG) * kStL + q];
-#pragma unroll
-      for (int i = 0; i < kStUnroll; ++i) s += v[i];
-    }
-    for (; b < nblk; b += NG) s += part[(size_t)b * kStL + q];
-  }
-  grp[g * Lp + q] = s;
+#pragma unroll 4
+  for (int b = t; b < nblk; b += kStBlock) s += row[b];
+  s = wave_sum(s);
+  if ((t & 63) == 0) red[t >> 6] = s;
   __syncthreads();
-#pragma unroll
-  for (int h = NG / 2; h >= 32; h >>= 1) {
-    if (g < h) grp[g * Lp + q] += grp[(g + h) * Lp + q];
-    __syncthreads();
-  }
-  if (t < L) {
-    double v = 0.0;
-    for (int r = 0; r < 32; ++r) v += grp[r * Lp + t];
-    out[t] = v;
+  if (t == 0) {
+    __hip_atomic_store(&ks->tot[v], (red[0] + red[1]) + (red[2] + red[3]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the total is out
+    *last = __hip_atomic_fetch_add(&ks->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x;
+    if (*last) ks->ticket = 0;
   }
   __syncthreads();
+  if (!*last) return false;
+  if (t < (int)gridDim.x) tot[t] = __hip_atomic_load(&ks->tot[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  return true;
 }
 
 __device__ __forceinline__ float st_weight(const FrameArgs& a, int p) {
@@ -170,57 +158,120 @@ __device__ __forceinline__ void st_set_y(StreamKS* ks, int j, double yv) {
   ks->yl[j] = (float)(yv - (double)hi);
 }
 
-// Frame start: y from the handle, flags cleared.
-__global__ void st_begin(FrameArgs a, StreamKS* ks) {
-  const int t = threadIdx.x;
-  if (t < kMaxK) st_set_y(ks, t, (t < a.k) ? a.y[t] : 0.0);
-  if (t == 0) {
-    ks->stop = ks->bad = ks->upd = ks->steps = ks->restarts = 0;
-    a.stats->frame = *a.nframe;
+// y of the passes: the handle's at the frame's first step (nothing is prepared
+// before it), the k-space state's after that.
+__device__ __forceinline__ void st_get_y(const FrameArgs& a, const StreamKS* ks, bool first, int j, float* ys,
+                                         float* yl) {
+  if (first) {
+    const double yv = (j < a.k) ? a.y[j] : 0.0;
+    ys[j] = (float)yv;
+    yl[j] = (float)(yv - (double)(float)yv);
+  } else {
+    ys[j] = ks->yf[j];
+    yl[j] = ks->yl[j];
   }
 }
 
-// Step 1 gradient pass at the current y (float32 per thread, as the frame kernel).
+// Step 1 gradient pass at the current y (float32 per thread, as the frame
+// kernel): partials of g, f and H's upper triangle row by row, value-major
+// (part[v * gridDim.x + workgroup]).  H: a wavefront leaves 64 rows of U and
+// their w c in LDS (its own, no barrier) and multiplies them in 16 steps of
+// v_mfma_f32_16x16x4f32: lane l holds column l % 16 of rows 16 (l / 16) + step
+// as one operand and the same times w c as the other, and one 16 x 16
+// float32 tile accumulates over all rows of the wavefront.
 template <int KC, typename TS, bool PAIR>
-__global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS* __restrict__ ks, float* __restrict__ wc,
-                                                    double* __restrict__ part) {
+__global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS* __restrict__ ks,
+                                                    double* __restrict__ part, int nchunk, bool first) {
   constexpr int N = StPix<TS, PAIR>::N;
-  if (ks->stop || ks->bad) return;
+  constexpr int NV = st_nh<KC>();
+  if (!first && (ks->stop || ks->bad)) return;
   __shared__ float ys[KC], yl[KC];
-  __shared__ double red[kStWaves][kStL];
-  const int tid = thread_index();
-  if (tid < KC) {
-    ys[tid] = ks->yf[tid];
-    yl[tid] = ks->yl[tid];
-  }
-  __syncthreads();
-  const int p0 = (blockIdx.x * kStBlock + tid) * N;
-  const bool valid = p0 < a.P;   // with pairs P is even, so both pixels are
-  float wt[N];
+  __shared__ __align__(16) float us[kStWaves][16][kStPad];
+  __shared__ __align__(16) float ws[kStWaves][64];
+  __shared__ double red[kStWaves][KC + 1];
+  const int tid = thread_index(), lane = tid & 63, wv = tid >> 6;
+  const int i16 = lane & 15, k4 = lane >> 4;
+  if (tid < KC) st_get_y(a, ks, first, tid, ys, yl);
 #pragma unroll
-  for (int i = 0; i < N; ++i) wt[i] = valid ? st_weight(a, p0 + i) : 0.f;
+  for (int j = KC; j < 16; ++j) us[wv][j][lane] = 0.f;
+  __syncthreads();
   float acc[KC + 1];
 #pragma unroll
   for (int j = 0; j <= KC; ++j) acc[j] = 0.f;
-  if (valid)
+  f32x4_t h = {0.f, 0.f, 0.f, 0.f};
+  for (int ch = blockIdx.x; ch < nchunk; ch += gridDim.x) {
+    const int p0 = (ch * kStBlock + tid) * N;
+    const bool valid = p0 < a.P;   // with pairs P is even, so both pixels are
+    float wt[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) wt[i] = valid ? st_weight(a, p0 + i) : 0.f;
     for (int c = 0; c < a.C; ++c) {
       float u[N][KC], x[N];
-      st_load<KC, TS, PAIR>(a, c, p0, u, x);
-      const long long e = (long long)c * a.P + p0;
+      if (valid) {
+        st_load<KC, TS, PAIR>(a, c, p0, u, x);
+      } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          x[i] = 0.f;
+#pragma unroll
+          for (int j = 0; j < KC; ++j) u[i][j] = 0.f;
+        }
+      }
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        const float r = st_residual<KC>(x[i], u[i], ys, yl);
-        float phi, cc;
-        cost_eval(r, a.cp, phi, cc);
-        const float w_c = wt[i] * cc;
-        wc[e + i] = w_c;
-        const float wd = w_c * r;                 // w phi'(r)
-        acc[KC] = fmaf(wt[i], phi, acc[KC]);
+        float w_c = 0.f;
+        if (valid) {
+          const float r = st_residual<KC>(x[i], u[i], ys, yl);
+          float phi, cc;
+          cost_eval(r, a.cp, phi, cc);
+          w_c = wt[i] * cc;
+          const float wd = w_c * r;                 // w phi'(r)
+          acc[KC] = fmaf(wt[i], phi, acc[KC]);
 #pragma unroll
-        for (int j = 0; j < KC; ++j) acc[j] = fmaf(wd, u[i][j], acc[j]);
+          for (int j = 0; j < KC; ++j) acc[j] = fmaf(wd, u[i][j], acc[j]);
+        }
+        wave_order();   // the rows before these have been read
+#pragma unroll
+        for (int j = 0; j < KC; ++j) us[wv][j][lane] = u[i][j];
+        ws[wv][lane] = w_c;
+        wave_order();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 uq = *(const float4*)&us[wv][i16][k4 * 16 + 4 * q];
+          const float4 wq = *(const float4*)&ws[wv][k4 * 16 + 4 * q];
+          h = __builtin_amdgcn_mfma_f32_16x16x4f32(uq.x, wq.x * uq.x, h, 0, 0, 0);
+          h = __builtin_amdgcn_mfma_f32_16x16x4f32(uq.y, wq.y * uq.y, h, 0, 0, 0);
+          h = __builtin_amdgcn_mfma_f32_16x16x4f32(uq.z, wq.z * uq.z, h, 0, 0, 0);
+          h = __builtin_amdgcn_mfma_f32_16x16x4f32(uq.w, wq.w * uq.w, h, 0, 0, 0);
+        }
       }
     }
-  st_block_partials<KC + 1>(acc, red, part);
+  }
+  {
+    int comp;
+    const float v = wave_reduce_scatter<KC + 1>(acc, comp);
+    if (wave_rs_owner<KC + 1>(lane) && comp <= KC) red[wv][comp] = (double)v;
+  }
+  wave_order();
+#pragma unroll
+  for (int v = 0; v < 4; ++v) us[wv][4 * k4 + v][i16] = h[v];   // H[row][column]
+  __syncthreads();
+  if (tid < NV) {
+    double s = 0.0;
+    if (tid <= KC) {
+#pragma unroll
+      for (int w = 0; w < kStWaves; ++w) s += red[w][tid];
+    } else {
+      int i = 0, t = tid - (KC + 1);
+      while (t >= KC - i) {
+        t -= KC - i;
+        ++i;
+      }
+#pragma unroll
+      for (int w = 0; w < kStWaves; ++w) s += (double)us[w][i][i + t];
+    }
+    part[(size_t)tid * gridDim.x + blockIdx.x] = s;
+  }
 }
 
 // PR+ direction from the reduced gradient and cost tot[0..KC] (the frame
@@ -284,163 +335,34 @@ __device__ __forceinline__ void st_adv_core(const FrameArgs& a, StreamKS* ks, do
   }
 }
 
-// Reduced gradient and cost -> PR+ direction (curvature schedule 0).
+// Sums of a gradient pass, then direction and majoriser step from them
+// (d^T H d: lane i row i of the triangle, rows added in order).
 template <int KC>
-__global__ __launch_bounds__(kStRed) void st_direction(FrameArgs a, StreamKS* ks, const double* __restrict__ part,
-                                                       int nblk, int it) {
-  if (ks->stop || ks->bad) return;
-  __shared__ double grp[kStRed];
-  __shared__ double tot[32];
-  st_sum_partials<KC + 1>(part, nblk, grp, tot);
-  if (threadIdx.x < 64) st_dir_core<KC>(a, ks, tot, it);
-}
-
-// Curvature of the majoriser along d: sum w c (u . d)^2.
-template <int KC, typename TS, bool PAIR>
-__global__ __launch_bounds__(kStBlock) void st_curv(FrameArgs a, const StreamKS* __restrict__ ks,
-                                                    const float* __restrict__ wc, double* __restrict__ part) {
-  constexpr int N = StPix<TS, PAIR>::N;
-  if (ks->stop || ks->bad) return;
-  __shared__ float ds[KC];
-  __shared__ double red[kStWaves][kStL];
-  const int tid = thread_index();
-  if (tid < KC) ds[tid] = ks->df[tid];
-  __syncthreads();
-  const int p0 = (blockIdx.x * kStBlock + tid) * N;
-  float acc[1] = {0.f};
-  if (p0 < a.P)
-    for (int c = 0; c < a.C; ++c) {
-      float u[N][KC], x[N];
-      st_load<KC, TS, PAIR>(a, c, p0, u, x);   // x unused: the compiler drops its load
-      const long long e = (long long)c * a.P + p0;
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        float t = 0.f;
-#pragma unroll
-        for (int j = 0; j < KC; ++j) t = fmaf(u[i][j], ds[j], t);
-        acc[0] = fmaf(wc[e + i] * t, t, acc[0]);
-      }
-    }
-  st_block_partials<1>(acc, red, part);
-}
-
-// Majoriser step: alpha = -g.d / d^T H d, y += alpha d.
-__global__ __launch_bounds__(kStRed) void st_advance(FrameArgs a, StreamKS* ks, const double* __restrict__ part,
-                                                     int nblk, int it) {
-  if (ks->stop || ks->bad) return;
-  __shared__ double grp[kStRed];
-  __shared__ double tot[32];
-  st_sum_partials<1>(part, nblk, grp, tot);
-  st_adv_core(a, ks, tot[0], it);
-}
-
-// Curvature schedule 1 (d^T H d from the reduced matrix H): one pass per CG
-// step reduces g, f and the upper triangle of H = U^T diag(w c) U together
-// (k (k + 1) / 2 more products per entry), so the curvature pass and its
-// launches drop out.  Partials value-major: part[v * nblk + workgroup].
-template <int KC, typename TS, bool PAIR>
-__global__ __launch_bounds__(kStBlock) void st_gradh(FrameArgs a, const StreamKS* __restrict__ ks,
-                                                     double* __restrict__ part, int nblk) {
-  constexpr int N = StPix<TS, PAIR>::N;
-  constexpr int NV = st_nh<KC>();
-  if (ks->stop || ks->bad) return;
-  __shared__ float ys[KC], yl[KC];
-  __shared__ double red[kStWaves][NV];
-  const int tid = thread_index(), lane = tid & 63, wv = tid >> 6;
-  if (tid < KC) {
-    ys[tid] = ks->yf[tid];
-    yl[tid] = ks->yl[tid];
-  }
-  __syncthreads();
-  const int p0 = (blockIdx.x * kStBlock + tid) * N;
-  const bool valid = p0 < a.P;
-  float wt[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) wt[i] = valid ? st_weight(a, p0 + i) : 0.f;
-  float acc[NV];   // g (KC), f, H upper triangle row by row
-#pragma unroll
-  for (int q = 0; q < NV; ++q) acc[q] = 0.f;
-  if (valid)
-    for (int c = 0; c < a.C; ++c) {
-      float u[N][KC], x[N];
-      st_load<KC, TS, PAIR>(a, c, p0, u, x);
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        const float r = st_residual<KC>(x[i], u[i], ys, yl);
-        float phi, cc;
-        cost_eval(r, a.cp, phi, cc);
-        const float w_c = wt[i] * cc;
-        const float wd = w_c * r;                 // w phi'(r)
-        acc[KC] = fmaf(wt[i], phi, acc[KC]);
-#pragma unroll
-        for (int j = 0; j < KC; ++j) acc[j] = fmaf(wd, u[i][j], acc[j]);
-        int q = KC + 1;
-#pragma unroll
-        for (int j = 0; j < KC; ++j) {
-          const float tj = w_c * u[i][j];
-#pragma unroll
-          for (int l = j; l < KC; ++l) {
-            acc[q] = fmaf(tj, u[i][l], acc[q]);
-            ++q;
-          }
-        }
-      }
-    }
-  // workgroup sums in chunks of 32 values (fixed order, float64 across wavefronts)
-#pragma unroll
-  for (int c0 = 0; c0 < NV; c0 += 32) {
-    float ch[32];
-#pragma unroll
-    for (int q = 0; q < 32; ++q) ch[q] = (c0 + q < NV) ? acc[(c0 + q < NV) ? c0 + q : 0] : 0.f;
-    int comp;
-    const float v = wave_reduce_scatter<32>(ch, comp);
-    if (wave_rs_owner<32>(lane) && c0 + comp < NV) red[wv][c0 + comp] = (double)v;
-  }
-  __syncthreads();
-  for (int q = tid; q < NV; q += kStBlock) {
-    double sum = 0.0;
-#pragma unroll
-    for (int w = 0; w < kStWaves; ++w) sum += red[w][q];
-    part[(size_t)q * nblk + blockIdx.x] = sum;
-  }
-}
-
-// Sum of value v's partials over the nblk workgroups (one workgroup per
-// value, fixed order) into ks->htot[v].
-__global__ __launch_bounds__(256) void st_hsum(StreamKS* ks, const double* __restrict__ part, int nblk) {
-  if (ks->stop || ks->bad) return;
-  __shared__ double red[4];
-  const int v = blockIdx.x, t = threadIdx.x;
-  const double* row = part + (size_t)v * nblk;
-  double s = 0.0;
-  for (int b = t; b < nblk; b += 256) s += row[b];
-  s = wave_sum(s);
-  if ((t & 63) == 0) red[t >> 6] = s;
-  __syncthreads();
-  if (t == 0) ks->htot[v] = (red[0] + red[1]) + (red[2] + red[3]);
-}
-
-// Direction and majoriser step of schedule 1: d^T H d from the reduced H.
-template <int KC>
-__global__ __launch_bounds__(64) void st_step(FrameArgs a, StreamKS* ks, int it) {
-  if (ks->stop || ks->bad) return;
-  __shared__ double tot[st_nh<KC>()];
-  __shared__ double dsh[KC];
-  for (int q = threadIdx.x; q < st_nh<KC>(); q += 64) tot[q] = ks->htot[q];
-  __syncthreads();
-  st_dir_core<KC>(a, ks, tot, it);
-  __syncthreads();
-  if (ks->stop || ks->bad) return;
-  if (threadIdx.x < KC) dsh[threadIdx.x] = ks->d[threadIdx.x];
-  __syncthreads();
-  // row i of the triangle by lane i, rows added in order
+__global__ __launch_bounds__(kStBlock) void st_step(FrameArgs a, StreamKS* ks, const double* __restrict__ part,
+                                                    int nblk, int it) {
+  if (it > 0 && (ks->stop || ks->bad)) return;
+  __shared__ double red[kStWaves];
+  __shared__ int last;
+  __shared__ double tot[kStWide];
   __shared__ double rowsum[KC];
-  const int i = threadIdx.x;
-  if (i < KC) {
-    int q = KC + 1 + i * KC - i * (i - 1) / 2;   // H[i][i]
-    double sacc = tot[q] * dsh[i] * dsh[i];
-    for (int l = i + 1; l < KC; ++l) sacc += 2.0 * tot[++q] * dsh[i] * dsh[l];
-    rowsum[i] = sacc;
+  if (!st_sum_value(ks, part, nblk, red, &last, tot)) return;
+  const int t = threadIdx.x;
+  if (it == 0) {   // frame start: y from the handle, flags cleared
+    if (t < kMaxK) st_set_y(ks, t, (t < a.k) ? a.y[t] : 0.0);
+    if (t == 0) {
+      ks->stop = ks->bad = ks->upd = ks->steps = ks->restarts = 0;
+      a.stats->frame = *a.nframe;
+    }
+    __syncthreads();
+  }
+  if (t < 64) st_dir_core<KC>(a, ks, tot, it);
+  __syncthreads();
+  if (ks->stop || ks->bad) return;
+  if (t < KC) {
+    int q = KC + 1 + t * KC - t * (t - 1) / 2;   // H[t][t]
+    double s = tot[q] * ks->d[t] * ks->d[t];
+    for (int l = t + 1; l < KC; ++l) s += 2.0 * tot[++q] * ks->d[t] * ks->d[l];
+    rowsum[t] = s;
   }
   __syncthreads();
   double dHd = 0.0;
@@ -452,26 +374,24 @@ __global__ __launch_bounds__(64) void st_step(FrameArgs a, StreamKS* ks, int it)
 // partials of U^T eta, ||eta||^2 and the final cost.
 template <int KC, typename TS, bool PAIR>
 __global__ __launch_bounds__(kStBlock) void st_eta(FrameArgs a, const StreamKS* __restrict__ ks, float* __restrict__ eta,
-                                                   double* __restrict__ part) {
+                                                   double* __restrict__ part, int nchunk) {
   constexpr int N = StPix<TS, PAIR>::N;
+  constexpr int L = KC + 2;
   if (ks->bad) return;
   __shared__ float ys[KC], yl[KC];
-  __shared__ double red[kStWaves][kStL];
-  const int tid = thread_index();
-  if (tid < KC) {
-    ys[tid] = ks->yf[tid];
-    yl[tid] = ks->yl[tid];
-  }
+  __shared__ double red[kStWaves][L];
+  const int tid = thread_index(), lane = tid & 63, wv = tid >> 6;
+  if (tid < KC) st_get_y(a, ks, false, tid, ys, yl);
   __syncthreads();
-  const int p0 = (blockIdx.x * kStBlock + tid) * N;
-  const bool valid = p0 < a.P;
-  float wt[N];
+  float acc[L];
 #pragma unroll
-  for (int i = 0; i < N; ++i) wt[i] = valid ? st_weight(a, p0 + i) : 0.f;
-  float acc[KC + 2];
+  for (int j = 0; j < L; ++j) acc[j] = 0.f;
+  for (int ch = blockIdx.x; ch < nchunk; ch += gridDim.x) {
+    const int p0 = (ch * kStBlock + tid) * N;
+    if (p0 >= a.P) continue;
+    float wt[N];
 #pragma unroll
-  for (int j = 0; j < KC + 2; ++j) acc[j] = 0.f;
-  if (valid)
+    for (int i = 0; i < N; ++i) wt[i] = st_weight(a, p0 + i);
     for (int c = 0; c < a.C; ++c) {
       float u[N][KC], x[N];
       st_load<KC, TS, PAIR>(a, c, p0, u, x);
@@ -489,18 +409,36 @@ __global__ __launch_bounds__(kStBlock) void st_eta(FrameArgs a, const StreamKS* 
         for (int j = 0; j < KC; ++j) acc[j] = fmaf(et, u[i][j], acc[j]);
       }
     }
-  st_block_partials<KC + 2>(acc, red, part);
+  }
+  int comp;
+  const float v = wave_reduce_scatter<L>(acc, comp);
+  if (wave_rs_owner<L>(lane) && comp < L) red[wv][comp] = (double)v;
+  __syncthreads();
+  if (tid < L) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kStWaves; ++w) s += red[w][tid];
+    part[(size_t)tid * gridDim.x + blockIdx.x] = s;
+  }
 }
 
-// Geodesic scalars (Sec. 3.3 Step 2, Sec. 3.4 step size) from the reduced
-// a = U^T eta, ||eta||^2 and the final cost, as geodesic_setup does.
+// Sums of the eta pass, then the geodesic scalars (Sec. 3.3 Step 2, Sec. 3.4
+// step size) as geodesic_setup forms them, and the end of the frame: y and the
+// frame counter (an accepted frame only; the update pass needs neither).
 template <int KC>
-__global__ __launch_bounds__(kStRed) void st_geodesic(FrameArgs a, StreamKS* ks, const double* __restrict__ part,
-                                                      int nblk) {
-  if (ks->bad) return;
-  __shared__ double grp[kStRed];
-  __shared__ double tot[32];
-  st_sum_partials<KC + 2>(part, nblk, grp, tot);
+__global__ __launch_bounds__(kStBlock) void st_geodesic(FrameArgs a, StreamKS* ks, const double* __restrict__ part,
+                                                        int nblk) {
+  if (ks->bad) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      a.stats->bad_frame = 1;
+      a.sync[4] = 0;
+    }
+    return;
+  }
+  __shared__ double red[kStWaves];
+  __shared__ int last;
+  __shared__ double tot[kStWide];
+  if (!st_sum_value(ks, part, nblk, red, &last, tot)) return;
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
     const double av = (lane < a.k) ? tot[lane] : 0.0;
@@ -516,6 +454,7 @@ __global__ __launch_bounds__(kStRed) void st_geodesic(FrameArgs a, StreamKS* ks,
       ks->af[lane] = (float)av;
       ks->vf[lane] = upd ? (float)(yv / nu) : 0.f;
     }
+    if (lane < a.k) a.y[lane] = yv;
     if (lane == 0) {
       const long long n = *a.nframe;
       const double t = step_size(a.tau * (double)n, a.t_init, a.t_min);
@@ -534,6 +473,9 @@ __global__ __launch_bounds__(kStRed) void st_geodesic(FrameArgs a, StreamKS* ks,
       a.stats->zeta = zeta;
       a.stats->nu = nu;
       a.stats->updated = upd;
+      a.stats->bad_frame = 0;
+      *a.nframe = n + 1;
+      a.sync[4] = 0;   // the mask is no longer the labels' median
     }
   }
 }
@@ -603,61 +545,35 @@ __global__ __launch_bounds__(kStBlock) void st_update(FrameArgs a, const StreamK
   for (int i = 0; i < N; ++i) a.lab[p0 + i] = label[i];
 }
 
-// Frame end: y and the frame counter (an accepted frame only).
-__global__ void st_end(FrameArgs a, const StreamKS* __restrict__ ks) {
-  const int t = threadIdx.x;
-  if (t == 0) a.sync[4] = 0;   // the mask is no longer the labels' median
-  if (ks->bad) {
-    if (t == 0) a.stats->bad_frame = 1;
-    return;
-  }
-  if (t < a.k) a.y[t] = ks->y[t];
-  if (t == 0) {
-    a.stats->bad_frame = 0;
-    *a.nframe = *a.nframe + 1;
-  }
-}
-
-// One frame: nblk workgroups of kStBlock threads, each thread one pixel (or
-// one pixel pair with PAIR).  a.curv selects the CG curvature schedule: 0,
-// d^T H d from a second pass over U per step; 1, H reduced with the gradient.
+// One frame: nchunk groups of kStBlock threads, each thread one pixel (or one
+// pixel pair with PAIR).
 template <int KC, typename TS, bool PAIR>
-static void st_frame_launch(const FrameArgs& a, StreamKS* ks, float* wc, float* eta, double* part, int nblk,
-                            hipStream_t s) {
-  hipLaunchKernelGGL(st_begin, dim3(1), dim3(64), 0, s, a, ks);
+static void st_frame_launch(const FrameArgs& a, StreamKS* ks, float* eta, double* part, int nchunk, hipStream_t s) {
+  const int nblk = st_blocks(nchunk);
   for (int it = 0; it < a.J; ++it) {
-    if (a.curv == 1) {
-      hipLaunchKernelGGL((st_gradh<KC, TS, PAIR>), dim3(nblk), dim3(kStBlock), 0, s, a, (const StreamKS*)ks, part,
-                         nblk);
-      hipLaunchKernelGGL(st_hsum, dim3(st_nh<KC>()), dim3(256), 0, s, ks, (const double*)part, nblk);
-      hipLaunchKernelGGL((st_step<KC>), dim3(1), dim3(64), 0, s, a, ks, it);
-      continue;
-    }
-    hipLaunchKernelGGL((st_grad<KC, TS, PAIR>), dim3(nblk), dim3(kStBlock), 0, s, a, (const StreamKS*)ks, wc, part);
-    hipLaunchKernelGGL((st_direction<KC>), dim3(1), dim3(kStRed), 0, s, a, ks, (const double*)part, nblk, it);
-    hipLaunchKernelGGL((st_curv<KC, TS, PAIR>), dim3(nblk), dim3(kStBlock), 0, s, a, (const StreamKS*)ks,
-                       (const float*)wc, part);
-    hipLaunchKernelGGL(st_advance, dim3(1), dim3(kStRed), 0, s, a, ks, (const double*)part, nblk, it);
+    hipLaunchKernelGGL((st_grad<KC, TS, PAIR>), dim3(nblk), dim3(kStBlock), 0, s, a, (const StreamKS*)ks, part, nchunk,
+                       it == 0);
+    hipLaunchKernelGGL((st_step<KC>), dim3(st_nh<KC>()), dim3(kStBlock), 0, s, a, ks, (const double*)part, nblk, it);
   }
-  hipLaunchKernelGGL((st_eta<KC, TS, PAIR>), dim3(nblk), dim3(kStBlock), 0, s, a, (const StreamKS*)ks, eta, part);
-  hipLaunchKernelGGL((st_geodesic<KC>), dim3(1), dim3(kStRed), 0, s, a, ks, (const double*)part, nblk);
-  hipLaunchKernelGGL((st_update<KC, TS, PAIR>), dim3(nblk), dim3(kStBlock), 0, s, a, (const StreamKS*)ks,
+  hipLaunchKernelGGL((st_eta<KC, TS, PAIR>), dim3(nblk), dim3(kStBlock), 0, s, a, (const StreamKS*)ks, eta, part,
+                     nchunk);
+  hipLaunchKernelGGL((st_geodesic<KC>), dim3(KC + 2), dim3(kStBlock), 0, s, a, ks, (const double*)part, nblk);
+  hipLaunchKernelGGL((st_update<KC, TS, PAIR>), dim3(nchunk), dim3(kStBlock), 0, s, a, (const StreamKS*)ks,
                      (const float*)eta);
-  hipLaunchKernelGGL(st_end, dim3(1), dim3(64), 0, s, a, (const StreamKS*)ks);
 }
 
 template <typename TS, bool PAIR>
-static void st_frame_class(int kc, const FrameArgs& a, StreamKS* ks, float* wc, float* eta, double* part, int nblk,
+static void st_frame_class(int kc, const FrameArgs& a, StreamKS* ks, float* eta, double* part, int nchunk,
                            hipStream_t s) {
   switch (kc) {
-    case 2: st_frame_launch<2, TS, PAIR>(a, ks, wc, eta, part, nblk, s); break;
-    case 4: st_frame_launch<4, TS, PAIR>(a, ks, wc, eta, part, nblk, s); break;
-    case 5: st_frame_launch<5, TS, PAIR>(a, ks, wc, eta, part, nblk, s); break;
-    case 8: st_frame_launch<8, TS, PAIR>(a, ks, wc, eta, part, nblk, s); break;
-    case 10: st_frame_launch<10, TS, PAIR>(a, ks, wc, eta, part, nblk, s); break;
-    case 12: st_frame_launch<12, TS, PAIR>(a, ks, wc, eta, part, nblk, s); break;
-    case 15: st_frame_launch<15, TS, PAIR>(a, ks, wc, eta, part, nblk, s); break;
-    default: st_frame_launch<16, TS, PAIR>(a, ks, wc, eta, part, nblk, s); break;
+    case 2: st_frame_launch<2, TS, PAIR>(a, ks, eta, part, nchunk, s); break;
+    case 4: st_frame_launch<4, TS, PAIR>(a, ks, eta, part, nchunk, s); break;
+    case 5: st_frame_launch<5, TS, PAIR>(a, ks, eta, part, nchunk, s); break;
+    case 8: st_frame_launch<8, TS, PAIR>(a, ks, eta, part, nchunk, s); break;
+    case 10: st_frame_launch<10, TS, PAIR>(a, ks, eta, part, nchunk, s); break;
+    case 12: st_frame_launch<12, TS, PAIR>(a, ks, eta, part, nchunk, s); break;
+    case 15: st_frame_launch<15, TS, PAIR>(a, ks, eta, part, nchunk, s); break;
+    default: st_frame_launch<16, TS, PAIR>(a, ks, eta, part, nchunk, s); break;
   }
 }
 
@@ -667,18 +583,18 @@ static int st_class(int k) {
 
 }  // namespace prost
 
-// Device buffers of the streamed path: k-space state, per-entry w c and eta,
+// Device buffers of the streamed path: k-space state, per-entry eta,
 // per-workgroup partials.
 pros_status prost_stream_alloc(pros_handle* h) {
   using namespace prost;
-  const int nblk = (h->P + kStBlock - 1) / kStBlock;
-  const size_t bytes = sizeof(StreamKS) + 2 * sizeof(float) * (size_t)h->m + sizeof(double) * (size_t)nblk * kStWide +
-                       1024;
+  const int nchunk = (h->P + kStBlock - 1) / kStBlock;   // one pixel per thread; pairs need half
+  const int nblk = std::min(nchunk, kStResident);
+  const size_t bytes = sizeof(StreamKS) + sizeof(float) * (size_t)h->m + sizeof(double) * (size_t)nblk * kStWide + 1024;
   hipError_t e = hipMalloc(&h->stream_ws, bytes);
   if (e != hipSuccess) return prost_host::set_error(PROS_ENOMEM, "streamed-frame buffers: %s", hipGetErrorString(e));
   e = hipMemsetAsync(h->stream_ws, 0, bytes, h->stream);
   if (e != hipSuccess) return prost_host::set_error(PROS_EHIP, "streamed-frame buffers: %s", hipGetErrorString(e));
-  h->stream_blocks = nblk;
+  h->stream_blocks = nchunk;
   return PROS_OK;
 }
 
@@ -686,8 +602,7 @@ pros_status prost_stream_frame(pros_handle* h, const prost::FrameArgs& a) {
   using namespace prost;
   char* base = (char*)h->stream_ws;
   StreamKS* ks = (StreamKS*)base;
-  float* wc = (float*)(base + ((sizeof(StreamKS) + 255) / 256) * 256);
-  float* eta = wc + h->m;
+  float* eta = (float*)(base + ((sizeof(StreamKS) + 255) / 256) * 256);
   double* part = (double*)(((uintptr_t)(eta + h->m) + 255) / 256 * 256);
   const int kc = st_class(h->k);
   if (h->prm.storage == PROS_BF16) {
@@ -695,11 +610,11 @@ pros_status prost_stream_frame(pros_handle* h, const prost::FrameArgs& a) {
     // are ldU apart with ldU a multiple of 64; the frame is the caller's)
     const bool pair = h->P % 2 == 0 && h->ldU % 2 == 0 && ((uintptr_t)a.x & 3u) == 0 && ((uintptr_t)a.U & 3u) == 0;
     if (pair)
-      st_frame_class<uint16_t, true>(kc, a, ks, wc, eta, part, (h->P / 2 + kStBlock - 1) / kStBlock, h->stream);
+      st_frame_class<uint16_t, true>(kc, a, ks, eta, part, (h->P / 2 + kStBlock - 1) / kStBlock, h->stream);
     else
-      st_frame_class<uint16_t, false>(kc, a, ks, wc, eta, part, h->stream_blocks, h->stream);
+      st_frame_class<uint16_t, false>(kc, a, ks, eta, part, h->stream_blocks, h->stream);
   } else {
-    st_frame_class<float, false>(kc, a, ks, wc, eta, part, h->stream_blocks, h->stream);
+    st_frame_class<float, false>(kc, a, ks, eta, part, h->stream_blocks, h->stream);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
