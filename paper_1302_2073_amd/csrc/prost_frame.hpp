@@ -288,14 +288,24 @@ __device__ __forceinline__ void poll_pair(const double* base, int n, size_t qstr
   if (L > 16 && ex1) vx += wait_tagged(p1 + 16, e1, ep, a, bad);
 }
 
+// Raises the gang's time-out bit and the workgroup's flag if a lane of this
+// wavefront gave up.
+__device__ __forceinline__ void wave_give_up(int bad, const FrameArgs& a, FrameSmem& sm) {
+  if (__any(bad) && (thread_index() & 63) == 0) {
+    sm.ctl[2] = 1;
+    __hip_atomic_fetch_or(&a.sync[2], kErrTimeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
 // Gather by the whole workgroup: the sum of n tagged slots, one row of sums per
 // wavefront into sm.got.  Lane l of wavefront w takes component l % 16 of slots
 // 4 w + l / 16, then those 4 kWaves further on: the slots' lines spread over all
 // wavefronts (measured: one wavefront that polls 32 lines of 16 values takes
 // longer than eight that poll four each), two in flight per lane.  Ends with a
-// barrier; false (in every thread, the gang's time-out bit raised) on time-out.
+// barrier; after a time-out sm.ctl[2] is set (a plain barrier and a flag: the
+// barrier that also reduces a predicate takes 0.2 us more).
 template <int L>
-__device__ __forceinline__ bool gather_slots(const double* base, int n, size_t qstride, unsigned ep,
+__device__ __forceinline__ void gather_slots(const double* base, int n, size_t qstride, unsigned ep,
                                              const FrameArgs& a, FrameSmem& sm) {
   const int lane = thread_index() & 63, wv = thread_index() >> 6;
   const int comp = lane & 15;
@@ -310,16 +320,8 @@ __device__ __forceinline__ bool gather_slots(const double* base, int n, size_t q
     sm.got[wv][comp] = v;
     if (16 + comp < L) sm.got[wv][16 + comp] = vx;
   }
-  return spin_end(bad, a);
-}
-
-// Raises the gang's time-out bit and the workgroup's flag if a lane of this
-// wavefront gave up.
-__device__ __forceinline__ void wave_give_up(int bad, const FrameArgs& a, FrameSmem& sm) {
-  if (__any(bad) && (thread_index() & 63) == 0) {
-    sm.ctl[2] = 1;
-    __hip_atomic_fetch_or(&a.sync[2], kErrTimeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  wave_give_up(bad, a, sm);
+  __syncthreads();
 }
 
 // The slot set of an exchange: it alternates with the epoch, so a workgroup
@@ -332,23 +334,28 @@ __device__ __forceinline__ int slot_set(const FrameArgs& a, unsigned ep) {
 
 // Gang-wide sum of L float partials per thread in the tagged exchanges 2 and 3.
 // The first wavefront publishes the workgroup's sums and, on return, holds the
-// totals in s_out[0..L) (LDS, written by itself): the k-space step that follows
-// runs in that wavefront, and the barrier at its end is the one that the other
-// wavefronts wait at, so an exchange costs two barriers (three in a workgroup
-// that gathers) instead of five.  After that barrier the caller checks
-// sm.ctl[2].  False (in every thread) when a gathering workgroup gave up.
+// totals in s_out[0..L - LATE) (LDS, written by itself): the k-space step that
+// follows runs in that wavefront, and the barrier at its end is the one that the
+// other wavefronts wait at, so an exchange costs two barriers (three in a
+// workgroup that gathers) instead of five.  After that barrier the caller checks
+// sm.ctl[2].
 //   3: every workgroup gathers all G slots (two alternating sets).
 //   2: the tiles t = x mod 8 form group x, whose first tile gathers them and
 //      writes the group sum into eight copies, one for each residue of the
 //      readers (two alternating sets); every first wavefront sums the groups.
+// The last LATE values (those that would take a second line of every slot) only
+// tile 0 needs, after the next barrier: its second wavefront sums them from the
+// slots meanwhile.  (As a 17th value of the exchange the final cost made the eta
+// exchange of k = 15 take 1.1 us longer than the gradient's.)
 // Per exchange with nothing in between (us): 226 workgroups 2.9 -> 2.6, 57:
 // 2.5 -> 2.3, 29 (exchange 3): 2.4 -> 1.9; with the exchanges below, a frame
 // with its mask read takes 89 us instead of 106 at 640x480x3, k = 15, float32,
 // 46 instead of 64 at 320x240x3, k = 10 (ordinary dispatch), 59 instead of 67
 // at 160x120x3, k = 15.
-template <int L>
-__device__ __forceinline__ bool gang_reduce_wave0(float (&acc)[L], const FrameArgs& a, const int tile, int& nbar,
+template <int L, int LATE>
+__device__ __forceinline__ void gang_reduce_wave0(float (&acc)[L], const FrameArgs& a, const int tile, int& nbar,
                                                   unsigned ebase, FrameSmem& sm, double* s_out) {
+  constexpr int LM = L - LATE;
   const int tid = thread_index(), lane = tid & 63, wv = tid >> 6;
   {
     int comp;
@@ -359,6 +366,7 @@ __device__ __forceinline__ bool gang_reduce_wave0(float (&acc)[L], const FrameAr
   const unsigned ep = (ebase + (unsigned)nbar) & 0xFFu;
   const int set = slot_set(a, ep);
   __syncthreads();
+  double* slots = a.part + (size_t)(a.sync_mode == 3 && set ? a.G : 0) * kSlot;
   if (tid < L) {
     double v = 0.0;
 #pragma unroll
@@ -366,59 +374,69 @@ __device__ __forceinline__ bool gang_reduce_wave0(float (&acc)[L], const FrameAr
     if (a.G == 1)
       s_out[tid] = v;   // a gang of one workgroup: its sums are the totals
     else
-      st_tagged(&a.part[((size_t)(a.sync_mode == 3 && set ? a.G : 0) + tile) * kSlot + tid], tag_value(v, ep));
+      st_tagged(&slots[(size_t)tile * kSlot + tid], tag_value(v, ep));
   }
   if (a.G == 1) {
     wave_order();
-    return true;
+    return;
   }
   trace_point(a, tile, 24 + 3 * nbar);
   const int comp = lane & 15;
   if (a.sync_mode == 3) {
-    if (!gather_slots<L>(a.part + (size_t)(set ? a.G : 0) * kSlot, a.G, kSlot, ep, a, sm)) return false;
-    if (tid < L) {
+    gather_slots<LM>(slots, a.G, kSlot, ep, a, sm);
+    if (tid < LM) {
       double v = 0.0;
 #pragma unroll
       for (int q = 0; q < kWaves; ++q) v += sm.got[q][tid];
       s_out[tid] = v;
     }
     wave_order();
-    return true;
-  }
-  double* gs = a.part + (size_t)(2 * a.G + set * kGroups * kReplicas) * kSlot;   // [copy][group]
-  if (tile < kGroups) {   // group leader: members tile, tile + 8, ...
-    const int n = (a.G - tile + kGroups - 1) / kGroups;
-    if (!gather_slots<L>(a.part + (size_t)tile * kSlot, n, (size_t)kGroups * kSlot, ep, a, sm)) return false;
+  } else {
+    double* gs = a.part + (size_t)(2 * a.G + set * kGroups * kReplicas) * kSlot;   // [copy][group]
+    if (tile < kGroups) {   // group leader: members tile, tile + 8, ...
+      const int n = (a.G - tile + kGroups - 1) / kGroups;
+      gather_slots<LM>(slots + (size_t)tile * kSlot, n, (size_t)kGroups * kSlot, ep, a, sm);
+      if (wv == 0 && sm.ctl[2] == 0) {
+        double v = 0.0, vx = 0.0;
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q) {
+          v += sm.got[q][comp];
+          if (16 + comp < LM) vx += sm.got[q][16 + comp];
+        }
+        for (int c = lane >> 4; c < kReplicas; c += 4) {
+          double* p = gs + (size_t)(c * kGroups + tile) * kSlot;
+          if (comp < LM) st_tagged(p + comp, tag_value(v, ep));
+          if (16 + comp < LM) st_tagged(p + 16 + comp, tag_value(vx, ep));
+        }
+      }
+      trace_point(a, tile, 25 + 3 * (nbar - 1));
+    }
     if (wv == 0) {
       double v = 0.0, vx = 0.0;
-#pragma unroll
-      for (int q = 0; q < kWaves; ++q) {
-        v += sm.got[q][comp];
-        if (16 + comp < L) vx += sm.got[q][16 + comp];
+      int bad = 0;
+      poll_pair<LM>(gs + (size_t)(tile & (kReplicas - 1)) * kGroups * kSlot, min(kGroups, a.G), kSlot, lane >> 4, 4,
+                    comp, ep, a, v, vx, bad);
+      v = swap_sum<16>(swap_sum<32>(v));
+      if (LM > 16) vx = swap_sum<16>(swap_sum<32>(vx));
+      if (lane < 16) {
+        if (comp < LM) s_out[comp] = v;
+        if (16 + comp < LM) s_out[16 + comp] = vx;
       }
-      for (int c = lane >> 4; c < kReplicas; c += 4) {
-        double* p = gs + (size_t)(c * kGroups + tile) * kSlot;
-        if (comp < L) st_tagged(p + comp, tag_value(v, ep));
-        if (16 + comp < L) st_tagged(p + 16 + comp, tag_value(vx, ep));
-      }
+      wave_give_up(bad, a, sm);
+      wave_order();
     }
-    trace_point(a, tile, 25 + 3 * (nbar - 1));
   }
-  if (wv == 0) {
-    double v = 0.0, vx = 0.0;
+  if (LATE > 0 && tile == 0 && wv == 1) {
     int bad = 0;
-    poll_pair<L>(gs + (size_t)(tile & (kReplicas - 1)) * kGroups * kSlot, min(kGroups, a.G), kSlot, lane >> 4, 4, comp,
-                 ep, a, v, vx, bad);
-    v = swap_sum<16>(swap_sum<32>(v));
-    if (L > 16) vx = swap_sum<16>(swap_sum<32>(vx));
-    if (lane < 16) {
-      if (comp < L) s_out[comp] = v;
-      if (16 + comp < L) s_out[16 + comp] = vx;
+#pragma unroll
+    for (int c = LM; c < L; ++c) {
+      double v = 0.0, none = 0.0;
+      for (int q = lane; q < a.G; q += 128) poll_pair<1>(slots + c, a.G, kSlot, q, 64, 0, ep, a, v, none, bad);
+      v = wave_sum(v);
+      if (lane == 0) s_out[c] = v;
     }
     wave_give_up(bad, a, sm);
-    wave_order();
   }
-  return true;
 }
 
 // Gang-wide sum of one float per thread in the tagged exchanges 2 and 3, in
@@ -606,14 +624,15 @@ __device__ __forceinline__ bool wave0_exchange(const FrameArgs& a) { return a.G 
 
 // Gang-wide sum of L float partials: the same float64 totals in every workgroup
 // of the gang, in s_out[0..L) for the first wavefront.  The caller's next
-// barrier makes them visible to the others; sm.ctl[2] is checked after it.
-template <int L>
+// barrier makes them visible to the others; sm.ctl[2] is checked after it.  The
+// last LATE of them reach tile 0 alone, and only with that barrier.
+template <int L, int LATE = 0>
 __device__ __forceinline__ bool gang_reduce(float (&acc)[L], const FrameArgs& a, const int tile, int& nbar,
                                             unsigned base, unsigned ebase, FrameSmem& sm, double* s_out) {
   trace_point(a, tile, 2 + 2 * nbar);
-  bool ok;
+  bool ok = true;
   if (wave0_exchange(a)) {
-    ok = gang_reduce_wave0<L>(acc, a, tile, nbar, ebase, sm, s_out);
+    gang_reduce_wave0<L, LATE>(acc, a, tile, nbar, ebase, sm, s_out);
   } else if (a.sync_mode == 1) {
     wg_reduce<L>(acc, sm.red, sm.wg);
     ok = gang_reduce_tagged<L>(sm.wg, a, tile, nbar, ebase, sm.big, s_out, sm.ctl, false);
@@ -782,14 +801,23 @@ __device__ __forceinline__ void pre_store(const FrameArgs& a, long long e, float
   a.pre_mean[e] = mn;
 }
 
+// Step size t = max(exp(-tau n) t_init, t_min) of frame n (Sec. 3.4).  Out of
+// line like geodesic_scalars.  It needs nothing but the frame index: a thread of
+// the second wavefront forms it while the first takes the frame's first
+// direction (0.4 us in the one lane that forms the angle otherwise).
+__device__ __attribute__((noinline)) double step_size(double tau_n, double t_init, double t_min) {
+  return fmax(exp(-tau_n) * t_init, t_min);
+}
+
 // PR+ conjugate direction from the reduced gradient and cost in ks.red
 // (Sec. 3.3, Step 1): wave 0, lane j owns component j.  Sets ks.d / df / gp,
 // ks.gd and the stop flag ks.flag[0]; a non-finite first cost marks the frame
 // bad (ks.flag[1]).
 template <int K>
-__device__ __forceinline__ void cg_direction(const FrameArgs& a, KSpace<kMaxK>& ks, int it, bool lead,
+__device__ __forceinline__ void cg_direction(const FrameArgs& a, KSpace<kMaxK>& ks, long long n, int it, bool lead,
                                              int& restarts) {
   const int tid = thread_index(), lane = tid & 63;
+  if (tid == 64 && it == 0) ks.t = step_size(a.tau * (double)n, a.t_init, a.t_min);
   if (tid < 64) {
     const double g = (lane < K) ? -ks.red[lane] : 0.0;
     const double f = ks.red[K];
@@ -901,7 +929,7 @@ __device__ __forceinline__ void irls_h_partials(const float (&wc)[ROWS], UF uval
 // order.  Sets ks.d / df, ks.gd, the stop flag (zero gradient or H not
 // positive definite) and, in the first step, the bad-frame flag.
 template <int K>
-__device__ __forceinline__ void irls_direction(const FrameArgs& a, FrameSmem& sm, int it, bool lead) {
+__device__ __forceinline__ void irls_direction(const FrameArgs& a, FrameSmem& sm, long long n, int it, bool lead) {
   KSpace<kMaxK>& ks = sm.ks;
   const double* tot = sm.wide_out;
   const int tid = thread_index(), lane = tid & 63;
@@ -917,6 +945,7 @@ __device__ __forceinline__ void irls_direction(const FrameArgs& a, FrameSmem& sm
     sm.hs[i][j] = v;
   }
   if (tid == 0) ks.flag[3] = 0;
+  if (tid == 64 && it == 0) ks.t = step_size(a.tau * (double)n, a.t_init, a.t_min);
   __syncthreads();
   if (tid < 64) {
     const double g = (lane < K) ? -tot[lane] : 0.0;
@@ -992,14 +1021,14 @@ __device__ __forceinline__ void irls_advance(const FrameArgs& a, KSpace<kMaxK>& 
 // 16-lane sum), into ks.red[K + 1].  Same value, up to rounding, as the
 // second pass sum_e w c (u_e . d)^2.
 template <int K>
-__device__ __forceinline__ void wide_cg_direction(const FrameArgs& a, FrameSmem& sm, int it, bool lead,
+__device__ __forceinline__ void wide_cg_direction(const FrameArgs& a, FrameSmem& sm, long long n, int it, bool lead,
                                                   int& restarts) {
   KSpace<kMaxK>& ks = sm.ks;
   const double* tot = sm.wide_out;
   const int tid = thread_index(), lane = tid & 63;
   if (tid <= K) ks.red[tid] = tot[tid];
   __syncthreads();
-  cg_direction<K>(a, ks, it, lead, restarts);
+  cg_direction<K>(a, ks, n, it, lead, restarts);
   if (tid < 64) {
     double t = 0.0;
     if (lane < K) {
@@ -1078,7 +1107,6 @@ __device__ __forceinline__ void geodesic_setup(const FrameArgs& a, KSpace<kMaxK>
       ks.scal[2] = (float)nu;
       ks.flag[2] = upd;
       if (lead) {
-        a.stats->f[steps] = ks.red[K + 1];
         a.stats->t = ks.t;
         a.stats->sigma = sigma;
         a.stats->theta = g.theta;
@@ -1109,21 +1137,14 @@ __device__ __forceinline__ void next_frame_begin(KSpace<kMaxK>& ks, TileCtx& t, 
   __syncthreads();
 }
 
-// The deferred median of the previous frame's labels, by thread t0 of nt, and
-// the frame's step size t = max(exp(-tau n) t_init, t_min) (Sec. 3.4), which
-// needs nothing but the frame index.  The labels of the whole gang are complete
-// once this frame's first exchange is, and no workgroup writes this frame's
-// labels before the last exchange, so the wavefronts that do not wait for the
-// gang do both during its first single-value exchange: neither then costs time
-// of its own (1.8 us of a 640x480x3 float32 frame, 2.5 in bfloat16, and 0.4 for
-// the step size's exponential in the one lane that forms the angle).
-__device__ __attribute__((noinline)) double step_size(double tau_n, double t_init, double t_min) {
-  return fmax(exp(-tau_n) * t_init, t_min);
-}
+// The deferred median of the previous frame's labels, by thread t0 of nt.  The
+// labels of the whole gang are complete once this frame's first exchange is,
+// and no workgroup writes this frame's labels before the last exchange, so the
+// wavefronts that do not wait for the gang form it during its first
+// single-value exchange, where it costs no time of its own (1.8 us of a
+// 640x480x3 float32 frame, 2.5 in bfloat16).
 template <bool SEQ>
-__device__ __forceinline__ void between_frames(const FrameArgs& a, KSpace<kMaxK>& ks, const TileCtx& t, int t0,
-                                               int nt) {
-  if (t0 == 0) ks.t = step_size(a.tau * (double)t.n, a.t_init, a.t_min);
+__device__ __forceinline__ void between_frames(const FrameArgs& a, const TileCtx& t, int t0, int nt) {
   if (SEQ && t.median == 2)
     median3x3_range<true>(a.lab, a.mask, a.W, a.H, t.p0, t.npx, t0, nt);
   else if (t.median)
@@ -1142,14 +1163,25 @@ __device__ __forceinline__ bool pixel_label(const uint8_t* s_flag, int C, int np
 // stores (read by other workgroups in the same launch).
 template <bool COH = false>
 __device__ __forceinline__ void write_labels(const FrameArgs& a, const uint8_t* s_flag, int p0, int npx) {
+  // four pixels per thread at a time, their flags read together: the LDS
+  // latency is paid once per four pixels
+  constexpr int kLabBatch = 4;
   __syncthreads();
-  for (int pl = thread_index(); pl < npx; pl += kBlock) {
-    uint8_t f = 0;
-    for (int c = 0; c < a.C; ++c) f |= s_flag[c * npx + pl];
-    if (COH)
-      __hip_atomic_store(&a.lab[p0 + pl], f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else
-      a.lab[p0 + pl] = f;
+  for (int pl0 = thread_index(); pl0 < npx; pl0 += kLabBatch * kBlock) {
+    uint8_t f[kLabBatch] = {0, 0, 0, 0};
+    for (int c = 0; c < a.C; ++c) {
+#pragma unroll
+      for (int b = 0; b < kLabBatch; ++b) f[b] |= s_flag[c * npx + min(pl0 + b * kBlock, npx - 1)];
+    }
+#pragma unroll
+    for (int b = 0; b < kLabBatch; ++b) {
+      const int pl = pl0 + b * kBlock;
+      if (pl >= npx) break;
+      if (COH)
+        __hip_atomic_store(&a.lab[p0 + pl], f[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else
+        a.lab[p0 + pl] = f[b];
+    }
   }
 }
 
@@ -1255,7 +1287,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
   }
   // ---- Step 1: CG on y ----
   int steps = 0, restarts = 0;
-  bool between = true;   // the previous median and this frame's step size are still to be formed
+  bool between = true;   // the previous frame's median is still to be formed
   for (int it = 0; it < a.J; ++it) {
     // phase A: gradient and cost at the current y
     float acc[K + 1];   // g, f
@@ -1279,11 +1311,11 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
         return false;
       float af = 1.0f;
       if (a.ysolve == 2) {   // IRLS: unit step along -H^{-1} g
-        irls_direction<K>(a, sm, it, ctx.lead);
+        irls_direction<K>(a, sm, ctx.n, it, ctx.lead);
         if (ks.flag[0]) break;
         irls_advance<K>(a, ks, it, ctx.lead);
       } else {               // CG / gradient descent with d^T H d from the reduced H
-        wide_cg_direction<K>(a, sm, it, ctx.lead, restarts);
+        wide_cg_direction<K>(a, sm, ctx.n, it, ctx.lead, restarts);
         if (ks.flag[0]) break;
         const double dHd = ks.red[K + 1];
         if (!(dHd > 0.0)) break;
@@ -1301,7 +1333,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
       continue;
     }
     if (!gang_reduce<K + 1>(acc, a, tile, nbar, ctx.base, ctx.ebase, sm, ks.red)) return false;
-    cg_direction<K>(a, ks, it, ctx.lead, restarts);
+    cg_direction<K>(a, ks, ctx.n, it, ctx.lead, restarts);
     if (sm.ctl[2]) return false;
     if (ks.flag[0]) break;
     // phase B: curvature of the majoriser along d; cw then holds u.d
@@ -1316,7 +1348,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
     }
     double dHd;
     if (!gang_reduce1(accb[0], a, tile, nbar, ctx.base, ctx.ebase, sm, dHd, [&] {
-          if (between) between_frames<SEQ>(a, ks, ctx, thread_index() - 64, kBlock - 64);
+          if (between) between_frames<SEQ>(a, ctx, thread_index() - 64, kBlock - 64);
         }))
       return false;
     if (wave0_exchange(a) && a.G > 1) between = false;
@@ -1327,7 +1359,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
     ++steps;
   }
   const bool bad = ks.flag[1] != 0;
-  if (between) between_frames<SEQ>(a, ks, ctx, thread_index(), kBlock);
+  if (between) between_frames<SEQ>(a, ctx, thread_index(), kBlock);
 
   if (!bad) {
     // ---- Step 2: eta pass (a = U^T eta, ||eta||^2, final cost) ----
@@ -1347,10 +1379,15 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
 #pragma unroll
       for (int j = 0; j < K; ++j) acce[j] = fmaf(eta, u[s][j], acce[j]);
     }
-    if (!gang_reduce<LE>(acce, a, tile, nbar, ctx.base, ctx.ebase, sm, ks.red)) return false;
-    if (EXT && tid == 0 && pupd) ks.pre_sum = ks.red[K + 2];
+    // the final cost and the deviation sum serve the statistics alone
+    constexpr int kLate = LE - (K + 1 > 16 ? K + 1 : LE < 16 ? LE : 16);
+    if (!gang_reduce<LE, kLate>(acce, a, tile, nbar, ctx.base, ctx.ebase, sm, ks.red)) return false;
     geodesic_setup<K>(a, ks, steps, ctx.lead);
     if (sm.ctl[2]) return false;
+    if (ctx.lead && tid == 0) {
+      a.stats->f[steps] = ks.red[K + 1];
+      if (EXT && pupd) ks.pre_sum = ks.red[K + 2];
+    }
     trace_point(a, tile, 60);
 
     // ---- Step 2 update + Step 3 labels, one pass over the register tile ----
@@ -1616,7 +1653,7 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
   if constexpr (SEQ) tid = thread_index();   // re-enters opaquely each frame (see the float32 tile)
   // ---- Step 1: CG on y ----
   int steps = 0, restarts = 0;
-  bool between = true;   // the previous median and this frame's step size are still to be formed
+  bool between = true;   // the previous frame's median is still to be formed
   for (int it = 0; it < a.J; ++it) {
     float acc[K + 1];   // g, f
 #pragma unroll
@@ -1659,7 +1696,7 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
       }
     }
     if (!gang_reduce<K + 1>(acc, a, tile, nbar, ctx.base, ctx.ebase, sm, ks.red)) return false;
-    cg_direction<K>(a, ks, it, ctx.lead, restarts);
+    cg_direction<K>(a, ks, ctx.n, it, ctx.lead, restarts);
     if (sm.ctl[2]) return false;
     if (ks.flag[0]) break;
     float accb[1] = {0.f};
@@ -1698,7 +1735,7 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
     }
     double dHd;
     if (!gang_reduce1(accb[0], a, tile, nbar, ctx.base, ctx.ebase, sm, dHd, [&] {
-          if (between) between_frames<SEQ>(a, ks, ctx, thread_index() - 64, kBlock - 64);
+          if (between) between_frames<SEQ>(a, ctx, thread_index() - 64, kBlock - 64);
         }))
       return false;
     if (wave0_exchange(a) && a.G > 1) between = false;
@@ -1723,7 +1760,7 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
     ++steps;
   }
   const bool bad = ks.flag[1] != 0;
-  if (between) between_frames<SEQ>(a, ks, ctx, thread_index(), kBlock);
+  if (between) between_frames<SEQ>(a, ctx, thread_index(), kBlock);
 
   if (!bad) {
     constexpr int LE = K + 2 + (EXT ? 1 : 0);   // a, ||eta||^2, f (+ pre-processing deviation sum)
@@ -1770,10 +1807,15 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
         acce[j] = fmaf(et[1], bf_hi(v), acce[j]);
       }
     }
-    if (!gang_reduce<LE>(acce, a, tile, nbar, ctx.base, ctx.ebase, sm, ks.red)) return false;
-    if (EXT && tid == 0 && pupd) ks.pre_sum = ks.red[K + 2];
+    // the final cost and the deviation sum serve the statistics alone
+    constexpr int kLate = LE - (K + 1 > 16 ? K + 1 : LE < 16 ? LE : 16);
+    if (!gang_reduce<LE, kLate>(acce, a, tile, nbar, ctx.base, ctx.ebase, sm, ks.red)) return false;
     geodesic_setup<K>(a, ks, steps, ctx.lead);
     if (sm.ctl[2]) return false;
+    if (ctx.lead && tid == 0) {
+      a.stats->f[steps] = ks.red[K + 1];
+      if (EXT && pupd) ks.pre_sum = ks.red[K + 2];
+    }
     trace_point(a, tile, 60);
 
     uint16_t* __restrict__ Uw = (uint16_t*)a.U;
