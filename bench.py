@@ -42,18 +42,13 @@ def pass_bytes(m, k, P, bu, bx, J=5):
 
 def streamed_bytes(m, k, P, bu, bx, J=5, curvature=0):
     """HBM bytes of one frame in the streamed form (frames too large for
-    resident register tiles): per CG step the gradient pass reads U, x and
-    the labels and writes w c per entry, the curvature pass reads U and w c
-    (curvature schedule 1: one pass reading U, x and the labels, H reduced
-    with the gradient); the eta pass reads U, x and the labels and writes
-    eta; the update pass reads U, x and eta, writes U and the labels (4-byte
-    w c and eta)."""
-    grad = m * k * bu + m * bx + P + 4 * m
-    curv = m * k * bu + 4 * m
+    resident register tiles), under either curvature schedule: a CG step
+    reads U, x and the labels once (H reduced with the gradient); the eta
+    pass reads U, x and the labels and writes eta; the update pass reads U, x
+    and eta, writes U and the labels (4-byte eta)."""
     eta = m * k * bu + m * bx + P + 4 * m
     upd = 2 * m * k * bu + m * bx + 4 * m + P
-    step = (m * k * bu + m * bx + P) if curvature == 1 else grad + curv
-    return J * step + eta + upd
+    return J * (m * k * bu + m * bx + P) + eta + upd
 
 
 def kernel_source_hash():

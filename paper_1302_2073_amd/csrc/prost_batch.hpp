@@ -62,7 +62,9 @@ __host__ __device__ constexpr int batch_class(int k) {
 
 // A stream descriptor copied into scalar registers (its words are uniform
 // across the workgroup), as kernel arguments are: held in vector registers
-// the fields would take room from the register tile.
+// the fields would take room from the register tile.  Its pointers are marked as
+// global memory: as loaded values they were reached with flat instructions (1215
+// in the k = 15 kernel), each of which the next LDS access waits for too.
 __device__ __forceinline__ FrameArgs load_uniform(const FrameArgs* __restrict__ p) {
   static_assert(sizeof(FrameArgs) % 4 == 0, "descriptor of 32-bit words");
   FrameArgs a;
@@ -71,6 +73,22 @@ __device__ __forceinline__ FrameArgs load_uniform(const FrameArgs* __restrict__ 
 #pragma unroll
   for (int i = 0; i < (int)(sizeof(FrameArgs) / 4); ++i) w[i] = __builtin_amdgcn_readfirstlane(src[i]);
   __builtin_memcpy(&a, w, sizeof(FrameArgs));
+  a.U = global_ptr(a.U);
+  a.x = global_ptr(a.x);
+  a.xtab = global_ptr(a.xtab);
+  a.lab = global_ptr(a.lab);
+  a.mask = global_ptr(a.mask);
+  a.y = global_ptr(a.y);
+  a.nframe = global_ptr(a.nframe);
+  a.stats = global_ptr(a.stats);
+  a.part = global_ptr(a.part);
+  a.sync = global_ptr(a.sync);
+  a.trace = global_ptr(a.trace);
+  a.pre_mean = global_ptr(a.pre_mean);
+  a.pre_m2 = global_ptr(a.pre_m2);
+  a.pre_stat = global_ptr(a.pre_stat);
+  a.score = global_ptr(a.score);
+  a.seq = global_ptr(a.seq);
   return a;
 }
 

@@ -31,6 +31,15 @@
 namespace prost {
 inline namespace PROST_BLOCK_NS {
 
+// A pointer that was itself loaded from memory (frame tables, the descriptors of
+// a batch), in the global address space: the compiler knows that only of kernel
+// arguments, and reaches through other pointers with flat instructions, which
+// wait for the LDS and the memory counters both.
+template <typename T>
+__device__ __forceinline__ T* global_ptr(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+}
+
 struct FrameArgs {
   void* U;               // K planes of ldU entries (storage type)
   const void* x;         // frame, m entries (storage type); used when xtab is NULL
@@ -776,6 +785,15 @@ __device__ __forceinline__ TileCtx tile_begin(const FrameArgs& a, const int tile
   return t;
 }
 
+// Colour plane of tile entry q = c * npx + pixel (at most 4 planes): compares
+// instead of an integer division per row and pass.
+__device__ __forceinline__ int plane_of(int q, int npx) {
+  return (q >= npx ? 1 : 0) + (q >= 2 * npx ? 1 : 0) + (q >= 3 * npx ? 1 : 0);
+}
+__device__ __forceinline__ float ld_f32(const float* base, unsigned boff) {
+  return *(const float*)((const char*)base + boff);
+}
+
 // Pre-processing of one frame entry (Sec. 3.4): with upd the entry joins the
 // running average (Welford update of mean and deviation sum; the new
 // deviation sum is added to m2_sum), then the frame value minus the average
@@ -1218,6 +1236,17 @@ __device__ __forceinline__ void tile_end(const FrameArgs& a, const int tile, KSp
   __syncthreads();   // shared scratch may be reused by the next tile
 }
 
+// One column of U as a buffer: a store at kNowhere lies past its end and is
+// dropped, so a tile is stored without a branch and a lane mask per entry (the
+// masks and the K base addresses did not fit the scalar registers: 1433 lane
+// reads for them in the k = 15 bfloat16 update).  640x480x3, k = 15, update pass:
+// 16 bfloat16 rows per thread 9.9 -> 5.1 us, 8 rows 6.5 -> 3.1, one frame's kernel
+// 55.6 -> 51.3; float32 160x120x3 2.8 -> 1.6.
+constexpr unsigned kNowhere = 0xFFFFFFF0u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t column_rows(void* col, int m, int entry_bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(col, 0, (unsigned)m * entry_bytes, 0x00027000);
+}
+
 // ---------------------------------------------------------------------------
 // float32 storage: row q = tid + s * kBlock of the tile, K floats per row
 // ---------------------------------------------------------------------------
@@ -1232,49 +1261,82 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
 
   // ---- load the register tile: U rows, residual r = x - U y, weights ----
   const float* __restrict__ Ug = (const float*)a.U;
-  const float* __restrict__ xg = (const float*)(a.xtab ? a.xtab[ctx.n % a.ring] : a.x);
+  const float* __restrict__ xg = (const float*)(a.xtab ? global_ptr(a.xtab[ctx.n % a.ring]) : a.x);
   const uint8_t* __restrict__ wsrc = a.weights_from_filtered ? a.mask : a.lab;
   float u[NR][K];
   float r[NR], wt[NR], cw[NR];
   int eix[NR];
+  // Rows past the tile's end: a tile of 16 rows per thread is chosen for whatever
+  // 8 do not hold, so its upper half is worked in pairs, up to the last one in use
+  // (80x60x1: 10 rows of 16, a frame with its mask 36 -> 33 us); a scalar compare
+  // per pair of rows.
+  auto past = [&](int s) { return NR == 16 && s >= 8 && (s & ~1) * kBlock >= ctx.nq; };
   bool u_pending = false;   // sequence: the registers hold an update not yet stored
   auto store_tile = [&]() {  // sequence: the register tile to the U planes
-    float* __restrict__ Uw = (float*)a.U;
 #pragma unroll
-    for (int s = 0; s < NR; ++s)
-      if (eix[s] >= 0) {
+    for (int j = 0; j < K; ++j) {   // a plane at a time: one base address held
+      if (j >= a.k) continue;
+      const __amdgpu_buffer_rsrc_t col = column_rows((float*)a.U + (long long)j * a.ldU, a.m, 4);
 #pragma unroll
-        for (int j = 0; j < K; ++j)
-          if (j < a.k) Uw[(long long)j * a.ldU + eix[s]] = u[s][j];
+      for (int s = 0; s < NR; ++s) {
+        if (past(s)) continue;
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(u[s][j]), col,
+                                              eix[s] >= 0 ? 4u * (unsigned)eix[s] : kNowhere, 0, 0);
       }
+    }
   };
   const bool pre = EXT && a.pre_mean != nullptr;   // compiled out without EXT
   const bool pupd = EXT && ks.pre_upd != 0;
   const float pinv_n = ks.pre_inv_n, pinv_s = ks.pre_inv_s;
   float m2sum = 0.f;
+  // Every load of the tile is asked for before any is used (a thread's rows one
+  // after the other cost a memory latency each: to the first exchange 640x480x3,
+  // k = 15 10.5 -> 9.3 us, 160x120x3 4.4 -> 3.6, 80x60x1, k = 5 4.4 -> 3.7).  A row past the tile's end takes the first entry's
+  // values; its weight is 0 and it is never written.  32-bit byte offsets from
+  // uniform plane bases: a resident frame's planes are far below 4 GB.
+  uint8_t fgl[NR];
+  unsigned ub[NR];
 #pragma unroll
-  for (int s = 0; s < NR; ++s) {
-    const int q = tid + s * kBlock;
+  for (int s = 0; s < NR; ++s) {   // rows that the passes leave out
     eix[s] = -1;
-    wt[s] = 0.f;
-    r[s] = 0.f;
+    r[s] = wt[s] = cw[s] = 0.f;
+    fgl[s] = 0;
 #pragma unroll
     for (int j = 0; j < K; ++j) u[s][j] = 0.f;
-    if (q < ctx.nq) {
-      const int c = q / ctx.npx;
-      const int pl = q - c * ctx.npx;
-      const int e = c * a.P + ctx.p0 + pl;
-      eix[s] = e;
-      wt[s] = wsrc[ctx.p0 + pl] ? a.omega : 1.0f;
-      float acc = xg[e];
-      if (pre) acc = pre_entry(a, e, acc, pupd, pinv_n, pinv_s, m2sum);
+  }
 #pragma unroll
-      for (int j = 0; j < K; ++j) {
-        if (j < a.k) u[s][j] = Ug[(long long)j * a.ldU + e];   // columns >= k stay 0
-        acc = fmaf(-u[s][j], ks.yf[j], acc);
-      }
-      r[s] = acc;
+  for (int s = 0; s < NR; ++s) {
+    if (past(s)) continue;
+    const int q = tid + s * kBlock;
+    const bool in = q < ctx.nq;
+    const int c = plane_of(q, ctx.npx);
+    const int pl = in ? q - c * ctx.npx : 0;
+    const int e = in ? c * a.P + ctx.p0 + pl : ctx.p0;
+    eix[s] = in ? e : -1;
+    fgl[s] = wsrc[ctx.p0 + pl];
+    ub[s] = 4u * (unsigned)e;
+    r[s] = ld_f32(xg, ub[s]);
+  }
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    if (j >= a.k) continue;   // columns >= k are 0
+    const float* col = Ug + (long long)j * a.ldU;
+#pragma unroll
+    for (int s = 0; s < NR; ++s) {
+      if (past(s)) continue;
+      u[s][j] = ld_f32(col, ub[s]);
     }
+  }
+#pragma unroll
+  for (int s = 0; s < NR; ++s) {
+    if (past(s)) continue;
+    const bool in = eix[s] >= 0;
+    wt[s] = in ? (fgl[s] ? a.omega : 1.0f) : 0.f;
+    float acc = r[s];
+    if (pre && in) acc = pre_entry(a, eix[s], acc, pupd, pinv_n, pinv_s, m2sum);
+#pragma unroll
+    for (int j = 0; j < K; ++j) acc = fmaf(-u[s][j], ks.yf[j], acc);
+    r[s] = in ? acc : 0.f;
   }
 
   for (int fi = 0;;) {   // frames of this launch; U stays in the registers between them
@@ -1295,6 +1357,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
     for (int j = 0; j <= K; ++j) acc[j] = 0.f;
 #pragma unroll
     for (int s = 0; s < NR; ++s) {
+      if (past(s)) continue;
       float phi, c;
       cost_eval(r[s], a.cp, phi, c);
       const float wc = wt[s] * c;
@@ -1323,6 +1386,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
       }
 #pragma unroll
       for (int s = 0; s < NR; ++s) {
+        if (past(s)) continue;
         float t = 0.f;
 #pragma unroll
         for (int j = 0; j < K; ++j) t = fmaf(u[s][j], ks.df[j], t);
@@ -1340,6 +1404,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
     float accb[1] = {0.f};
 #pragma unroll
     for (int s = 0; s < NR; ++s) {
+      if (past(s)) continue;
       float t = 0.f;
 #pragma unroll
       for (int j = 0; j < K; ++j) t = fmaf(u[s][j], ks.df[j], t);
@@ -1370,6 +1435,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
     if constexpr (EXT) acce[LE - 1] = pupd ? m2sum : 0.f;
 #pragma unroll
     for (int s = 0; s < NR; ++s) {
+      if (past(s)) continue;
       float phi, c;
       cost_eval(r[s], a.cp, phi, c);
       const float eta = -wt[s] * c * r[s];
@@ -1391,7 +1457,6 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
     trace_point(a, tile, 60);
 
     // ---- Step 2 update + Step 3 labels, one pass over the register tile ----
-    float* __restrict__ Uw = (float*)a.U;
     const float cm1 = ks.scal[0], sz = ks.scal[1], nu_f = ks.scal[2];
     const bool upd = ks.flag[2] != 0;
     // a sequence keeps U in the registers (the next frame starts from them)
@@ -1401,6 +1466,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
     if (SEQ && upd) u_pending = !store_u;
 #pragma unroll
     for (int s = 0; s < NR; ++s) {
+      if (past(s)) continue;
       const int q = tid + s * kBlock;
       if (eix[s] >= 0) {
         float rl = r[s];
@@ -1413,11 +1479,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
           }
           const float coef = fmaf(cm1, uv, -sz * (cw[s] - ua));
 #pragma unroll
-          for (int j = 0; j < K; ++j) {
-            const float nv = fmaf(coef, ks.vf[j], u[s][j]);   // columns >= k stay 0 (v_j = 0)
-            if constexpr (SEQ) u[s][j] = nv;
-            else if (j < a.k) Uw[(long long)j * a.ldU + eix[s]] = nv;
-          }
+          for (int j = 0; j < K; ++j) u[s][j] = fmaf(coef, ks.vf[j], u[s][j]);   // columns >= k stay 0 (v_j = 0)
           if (a.labels_after_update) rl = fmaf(-coef, nu_f, rl);
         }
         if (pre && pupd) pre_store(a, eix[s], xg[eix[s]], pinv_n);
@@ -1425,7 +1487,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
         s_flag[q] = (fabsf(rl) >= a.delta) ? 1 : 0;
       }
     }
-    if (SEQ && upd && store_u) store_tile();
+    if (upd && store_u) store_tile();
     trace_point(a, tile, 61);
     write_labels<SEQ>(a, s_flag, ctx.p0, ctx.npx);
     trace_point(a, tile, 62);
@@ -1436,17 +1498,26 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
   // ---- next frame of a sequence: weights from this frame's labels (still in
   // s_flag; unchanged after a rejected frame), residuals of the next frame ----
   next_frame_begin(ks, ctx, bad);
-  xg = (const float*)(a.xtab ? a.xtab[ctx.n % a.ring] : a.seq[fi]);
+  xg = (const float*)(global_ptr(a.xtab ? a.xtab[ctx.n % a.ring] : a.seq[fi]));
+#pragma unroll
+  for (int s = 0; s < NR; ++s) r[s] = ld_f32(xg, 4u * (unsigned)(eix[s] >= 0 ? eix[s] : ctx.p0));
+  if (!bad) {
+#pragma unroll
+    for (int s = 0; s < NR; ++s) {
+      if (past(s)) continue;
+      const int q = tid + s * kBlock;
+      const int pl = eix[s] >= 0 ? q - plane_of(q, ctx.npx) * ctx.npx : 0;
+      const float wn = pixel_label(s_flag, a.C, ctx.npx, pl) ? a.omega : 1.0f;
+      wt[s] = eix[s] >= 0 ? wn : 0.f;
+    }
+  }
 #pragma unroll
   for (int s = 0; s < NR; ++s) {
-    if (eix[s] < 0) continue;
-    const int q = tid + s * kBlock;
-    const int pl = q - (q / ctx.npx) * ctx.npx;
-    if (!bad) wt[s] = pixel_label(s_flag, a.C, ctx.npx, pl) ? a.omega : 1.0f;
-    float acc = xg[eix[s]];
+    if (past(s)) continue;
+    float acc = r[s];
 #pragma unroll
     for (int j = 0; j < K; ++j) acc = fmaf(-u[s][j], ks.yf[j], acc);
-    r[s] = acc;
+    r[s] = eix[s] >= 0 ? acc : 0.f;
   }
   }
   // the last frame stored nothing (rejected, or no step): store the updated tile
@@ -1523,7 +1594,7 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
 
   // ---- load the register tile ----
   const uint16_t* __restrict__ Ug = (const uint16_t*)a.U;
-  const uint16_t* __restrict__ xg = (const uint16_t*)(a.xtab ? a.xtab[ctx.n % a.ring] : a.x);
+  const uint16_t* __restrict__ xg = (const uint16_t*)(a.xtab ? global_ptr(a.xtab[ctx.n % a.ring]) : a.x);
   const uint8_t* __restrict__ wsrc = a.weights_from_filtered ? a.mask : a.lab;
   uint32_t u[NP][K];
   // cw: w c in phase A, u.d in phase B, eta in the update (register rows);
@@ -1538,85 +1609,111 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
   const bool pupd = EXT && ks.pre_upd != 0;
   const float pinv_n = ks.pre_inv_n, pinv_s = ks.pre_inv_s;
   float m2sum = 0.f;
-#pragma unroll
-  for (int s = 0; s < NP; ++s) {
+  // Loads first, as in the float32 tile (640x480x3, k = 15, 16 rows per thread:
+  // 14.3 -> 8.9 us to the first exchange; 8 rows 8.0 -> 5.9).  A pair past the
+  // tile's end takes the first entry's values.  The pairs held in LDS go before the
+  // register pairs, while the registers are free.
+  // byte offsets in 32 bits from uniform plane bases: the addresses are a
+  // scalar base plus one vector offset, not 64-bit vector arithmetic
+  auto offsets = [&](int s, unsigned& b0, unsigned& b1) -> int {   // returns the pair's pixel in the tile
     const int q0 = 2 * (tid + s * kBlock);
-    r[2 * s] = r[2 * s + 1] = 0.f;
+    const bool in = q0 < ctx.nq, has1 = q0 + 1 < ctx.nq;
+    const int c = plane_of(q0, ctx.npx);
+    const int pl = in ? q0 - c * ctx.npx : 0;
+    const int e = in ? c * a.P + ctx.p0 + pl : ctx.p0;
+    const bool split = in && pl + 1 == ctx.npx;
+    b0 = 2u * (unsigned)e;
+    b1 = 2u * (unsigned)(!has1 ? e : split ? e + 1 + (a.P - ctx.npx) : e + 1);
+    if (in) vbits |= (has1 ? 3u : 1u) << (2 * s);
+    if (split) sbits |= 1u << s;
+    return pl;
+  };
+  auto labels = [&](int s, int pl, uint8_t& f0, uint8_t& f1) {
+    const bool one = (vbits >> (2 * s + 1)) & 1u;
+    f0 = wsrc[ctx.p0 + pl];
+    f1 = wsrc[ctx.p0 + (((sbits >> s) & 1u) || !one ? 0 : pl + 1)];
+  };
+  auto set_fbits = [&](int s, uint8_t f0, uint8_t f1) {
+    fbits |= (((f0 ? 1u : 0u) | (f1 ? 2u : 0u)) << (2 * s)) & vbits;
+  };
+  // The loads of NN pairs from pair s0 on.  The two forms of a pair (one word, or
+  // two halves to be put together) are told apart once for all of them: with the
+  // choice inside, every load of halves was waited for before the next.
+  auto load_pairs = [&](auto first, uint32_t* xw, uint32_t (*w)[K], uint8_t* f0, uint8_t* f1, auto count) {
+    constexpr int s0 = decltype(first)::value, nn = decltype(count)::value;
+    unsigned b0[nn], b1[nn];
 #pragma unroll
-    for (int j = 0; j < K; ++j) u[s][j] = 0u;
-    if (q0 < ctx.nq) {
-      const int c = q0 / ctx.npx;
-      const int pl = q0 - c * ctx.npx;
-      const int e = c * a.P + ctx.p0 + pl;
-      const bool has1 = q0 + 1 < ctx.nq;
-      const bool split = (pl + 1 == ctx.npx);
-      const int e1 = split ? e + 1 + (a.P - ctx.npx) : e + 1;
-      vbits |= (has1 ? 3u : 1u) << (2 * s);
-      if (split) sbits |= 1u << s;
-      if (wsrc[ctx.p0 + pl]) fbits |= 1u << (2 * s);
-      if (has1 && wsrc[ctx.p0 + (split ? 0 : pl + 1)]) fbits |= 2u << (2 * s);
-      // byte offsets in 32 bits from uniform plane bases: the addresses are a
-      // scalar base plus one vector offset, not 64-bit vector arithmetic
-      const unsigned b0 = 2u * (unsigned)e, b1 = 2u * (unsigned)e1;
-      uint32_t xw;
-      if (al) xw = ld_u32(xg, b0);
-      else xw = ld_u16(xg, b0) | (has1 ? (ld_u16(xg, b1) << 16) : 0u);
-      float acc0 = bf_lo(xw), acc1 = bf_hi(xw);
-      if (pre) {
+    for (int i = 0; i < nn; ++i) {
+      const int pl = offsets(s0 + i, b0[i], b1[i]);
+      labels(s0 + i, pl, f0[i], f1[i]);
+    }
+    if (al) {
+#pragma unroll
+      for (int i = 0; i < nn; ++i) xw[i] = ld_u32(xg, b0[i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < nn; ++i) xw[i] = ld_u16(xg, b0[i]) | (ld_u16(xg, b1[i]) << 16);
+    }
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      const uint16_t* col = Ug + (long long)j * a.ldU;
+      if (j >= a.k) {   // columns >= k are 0
+#pragma unroll
+        for (int i = 0; i < nn; ++i) w[i][j] = 0u;
+      } else if (al) {
+#pragma unroll
+        for (int i = 0; i < nn; ++i) w[i][j] = ld_u32(col, b0[i]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < nn; ++i) w[i][j] = ld_u16(col, b0[i]) | (ld_u16(col, b1[i]) << 16);
+      }
+    }
+  };
+  if constexpr (NL > 0) {
+    uint32_t v[NL][K], xw[NL];
+    uint8_t f0[NL], f1[NL];
+    load_pairs(std::integral_constant<int, NP>(), xw, v, f0, f1, std::integral_constant<int, NL>());
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int s = NP + i;
+      set_fbits(s, f0[i], f1[i]);
+      uint32_t* lts = lt + i * K * kBlock + tid;
+      float* rls = lr + i * 2 * kBlock + tid;
+      float acc0 = bf_lo(xw[i]), acc1 = bf_hi(xw[i]);
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+        lts[j * kBlock] = v[i][j];
+        acc0 = fmaf(-bf_lo(v[i][j]), ks.yf[j], acc0);
+        acc1 = fmaf(-bf_hi(v[i][j]), ks.yf[j], acc1);
+      }
+      rls[0] = ((vbits >> (2 * s)) & 1u) ? acc0 : 0.f;
+      rls[kBlock] = ((vbits >> (2 * s + 1)) & 1u) ? acc1 : 0.f;
+    }
+  }
+  {
+    uint32_t xw[NP];
+    uint8_t f0[NP], f1[NP];
+    load_pairs(std::integral_constant<int, 0>(), xw, u, f0, f1, std::integral_constant<int, NP>());
+#pragma unroll
+    for (int s = 0; s < NP; ++s) {
+      set_fbits(s, f0[s], f1[s]);
+      const bool in = (vbits >> (2 * s)) & 1u, has1 = (vbits >> (2 * s + 1)) & 1u;
+      float acc0 = bf_lo(xw[s]), acc1 = bf_hi(xw[s]);
+      if (pre && in) {
+        const int q0 = 2 * (tid + s * kBlock);
+        const int c = plane_of(q0, ctx.npx);
+        const int e = c * a.P + ctx.p0 + (q0 - c * ctx.npx);
         acc0 = pre_entry(a, e, acc0, pupd, pinv_n, pinv_s, m2sum);
-        if (has1) acc1 = pre_entry(a, e1, acc1, pupd, pinv_n, pinv_s, m2sum);
+        if (has1)
+          acc1 = pre_entry(a, ((sbits >> s) & 1u) ? e + 1 + (a.P - ctx.npx) : e + 1, acc1, pupd, pinv_n, pinv_s, m2sum);
       }
 #pragma unroll
       for (int j = 0; j < K; ++j) {
-        if (j < a.k) {
-          const uint16_t* col = Ug + (long long)j * a.ldU;
-          u[s][j] = al ? ld_u32(col, b0) : (ld_u16(col, b0) | (has1 ? (ld_u16(col, b1) << 16) : 0u));
-        }
         acc0 = fmaf(-bf_lo(u[s][j]), ks.yf[j], acc0);
         acc1 = fmaf(-bf_hi(u[s][j]), ks.yf[j], acc1);
       }
-      r[2 * s] = acc0;
+      r[2 * s] = in ? acc0 : 0.f;
       r[2 * s + 1] = has1 ? acc1 : 0.f;
-    }
-  }
-#pragma unroll 1
-  for (int s = NP; s < NT; ++s) {   // pairs held in LDS: the same load
-    const int q0 = 2 * (tid + s * kBlock);
-    uint32_t* lts = lt + (s - NP) * K * kBlock + tid;
-    float* rls = lr + (s - NP) * 2 * kBlock + tid;
-    rls[0] = rls[kBlock] = 0.f;
-    if (q0 < ctx.nq) {
-      const int c = q0 / ctx.npx;
-      const int pl = q0 - c * ctx.npx;
-      const int e = c * a.P + ctx.p0 + pl;
-      const bool has1 = q0 + 1 < ctx.nq;
-      const bool split = (pl + 1 == ctx.npx);
-      const int e1 = split ? e + 1 + (a.P - ctx.npx) : e + 1;
-      vbits |= (has1 ? 3u : 1u) << (2 * s);
-      if (split) sbits |= 1u << s;
-      if (wsrc[ctx.p0 + pl]) fbits |= 1u << (2 * s);
-      if (has1 && wsrc[ctx.p0 + (split ? 0 : pl + 1)]) fbits |= 2u << (2 * s);
-      const unsigned b0 = 2u * (unsigned)e, b1 = 2u * (unsigned)e1;
-      uint32_t xw;
-      if (al) xw = ld_u32(xg, b0);
-      else xw = ld_u16(xg, b0) | (has1 ? (ld_u16(xg, b1) << 16) : 0u);
-      float acc0 = bf_lo(xw), acc1 = bf_hi(xw);
-#pragma unroll
-      for (int j = 0; j < K; ++j) {
-        uint32_t v = 0u;
-        if (j < a.k) {
-          const uint16_t* col = Ug + (long long)j * a.ldU;
-          v = al ? ld_u32(col, b0) : (ld_u16(col, b0) | (has1 ? (ld_u16(col, b1) << 16) : 0u));
-        }
-        lts[j * kBlock] = v;
-        acc0 = fmaf(-bf_lo(v), ks.yf[j], acc0);
-        acc1 = fmaf(-bf_hi(v), ks.yf[j], acc1);
-      }
-      rls[0] = acc0;
-      rls[kBlock] = has1 ? acc1 : 0.f;
-    } else {
-#pragma unroll
-      for (int j = 0; j < K; ++j) lts[j * kBlock] = 0u;
     }
   }
   const float om = a.omega;
@@ -1626,26 +1723,30 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
   static_assert(!(SEQ && NL > 0), "sequences keep register tiles only");
   bool u_pending = false;   // sequence: the registers hold an update not yet stored
   auto store_tile = [&]() {  // sequence: the register tile to the U planes
-    uint16_t* __restrict__ Uw = (uint16_t*)a.U;
+    unsigned b0[NP], b1[NP];
 #pragma unroll
     for (int s = 0; s < NP; ++s) {
       const int q0 = 2 * (tid + s * kBlock);
-      if (q0 >= ctx.nq) continue;
-      const bool has1 = (vbits >> (2 * s + 1)) & 1u;
-      const int c = q0 / ctx.npx;
-      const int e = c * a.P + ctx.p0 + (q0 - c * ctx.npx);
-      const int e1 = ((sbits >> s) & 1u) ? e + 1 + (a.P - ctx.npx) : e + 1;
+      const int c = plane_of(q0, ctx.npx);
+      const unsigned b = 2u * (unsigned)(c * a.P + ctx.p0 + (q0 - c * ctx.npx));
+      const unsigned next = b + 2u + (((sbits >> s) & 1u) ? 2u * (unsigned)(a.P - ctx.npx) : 0u);
+      b0[s] = ((vbits >> (2 * s)) & 1u) ? b : kNowhere;
+      b1[s] = ((vbits >> (2 * s + 1)) & 1u) ? next : kNowhere;
+    }
 #pragma unroll
-      for (int j = 0; j < K; ++j)
-        if (j < a.k) {
-          uint16_t* col = Uw + (long long)j * a.ldU;
-          if (al) {
-            st_u32(col, 2u * (unsigned)e, u[s][j]);
-          } else {
-            st_u16(col, 2u * (unsigned)e, (uint16_t)(u[s][j] & 0xFFFFu));
-            if (has1) st_u16(col, 2u * (unsigned)e1, (uint16_t)(u[s][j] >> 16));
-          }
+    for (int j = 0; j < K; ++j) {   // a plane at a time: one base address held
+      if (j >= a.k) continue;
+      const __amdgpu_buffer_rsrc_t col = column_rows((uint16_t*)a.U + (long long)j * a.ldU, a.m, 2);
+      if (al) {
+#pragma unroll
+        for (int s = 0; s < NP; ++s) __builtin_amdgcn_raw_buffer_store_b32(u[s][j], col, b0[s], 0, 0);
+      } else {
+#pragma unroll
+        for (int s = 0; s < NP; ++s) {
+          __builtin_amdgcn_raw_buffer_store_b16((uint16_t)u[s][j], col, b0[s], 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(u[s][j] >> 16), col, b1[s], 0, 0);
         }
+      }
     }
   };
 
@@ -1832,7 +1933,7 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
       const int q0 = 2 * (tid + s * kBlock);
       if (q0 >= ctx.nq) continue;
       const bool has1 = (vbits >> (2 * s + 1)) & 1u;
-      const int c = q0 / ctx.npx;
+      const int c = plane_of(q0, ctx.npx);
       const int e = c * a.P + ctx.p0 + (q0 - c * ctx.npx);
       const int e1 = ((sbits >> s) & 1u) ? e + 1 + (a.P - ctx.npx) : e + 1;
       float rl0 = r[2 * s], rl1 = r[2 * s + 1];
@@ -1850,19 +1951,8 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
         const float coef1 = fmaf(cm1, uv1, -sz * (cw[2 * s + 1] - ua1));
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-          if constexpr (SEQ) {   // columns >= k stay 0 (v_j = 0)
-            u[s][j] = pack_bf16_rne(fmaf(coef0, ks.vf[j], bf_lo(u[s][j])), fmaf(coef1, ks.vf[j], bf_hi(u[s][j])));
-          } else if (j < a.k) {
-            const uint32_t nw = pack_bf16_rne(fmaf(coef0, ks.vf[j], bf_lo(u[s][j])),
-                                              fmaf(coef1, ks.vf[j], bf_hi(u[s][j])));
-            uint16_t* col = Uw + (long long)j * a.ldU;
-            if (al) {
-              st_u32(col, 2u * (unsigned)e, nw);
-            } else {
-              st_u16(col, 2u * (unsigned)e, (uint16_t)(nw & 0xFFFFu));
-              if (has1) st_u16(col, 2u * (unsigned)e1, (uint16_t)(nw >> 16));
-            }
-          }
+          // columns >= k stay 0 (v_j = 0)
+          u[s][j] = pack_bf16_rne(fmaf(coef0, ks.vf[j], bf_lo(u[s][j])), fmaf(coef1, ks.vf[j], bf_hi(u[s][j])));
         }
         if (a.labels_after_update) {
           rl0 = fmaf(-coef0, nu_f, rl0);
@@ -1880,7 +1970,7 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
       s_flag[q0] = (fabsf(rl0) >= a.delta) ? 1 : 0;
       if (has1) s_flag[q0 + 1] = (fabsf(rl1) >= a.delta) ? 1 : 0;
     }
-    if (SEQ && upd && store_u) store_tile();
+    if (upd && store_u) store_tile();
 #pragma unroll 1
     for (int s = NP; s < NT; ++s) {   // LDS pairs (no optional features)
       const int q0 = 2 * (tid + s * kBlock);
@@ -1888,7 +1978,7 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
       const uint32_t* lts = lt + (s - NP) * K * kBlock + tid;
       float* rls = lr + (s - NP) * 2 * kBlock + tid;
       const bool has1 = (vbits >> (2 * s + 1)) & 1u;
-      const int c = q0 / ctx.npx;
+      const int c = plane_of(q0, ctx.npx);
       const int e = c * a.P + ctx.p0 + (q0 - c * ctx.npx);
       const int e1 = ((sbits >> s) & 1u) ? e + 1 + (a.P - ctx.npx) : e + 1;
       float rl0 = rls[0], rl1 = rls[kBlock];
@@ -1943,34 +2033,40 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
 
   // ---- next frame of a sequence (as in the float32 tile) ----
   next_frame_begin(ks, ctx, bad);
-  xg = (const uint16_t*)(a.xtab ? a.xtab[ctx.n % a.ring] : a.seq[fi]);
+  xg = (const uint16_t*)(global_ptr(a.xtab ? a.xtab[ctx.n % a.ring] : a.seq[fi]));
+#pragma unroll
+  for (int s = 0; s < NP; ++s) {   // both entries of a pair into the first's register
+    const int q0 = 2 * (tid + s * kBlock);
+    const bool in = q0 < ctx.nq, has1 = q0 + 1 < ctx.nq;
+    const int c = plane_of(q0, ctx.npx);
+    const int e = in ? c * a.P + ctx.p0 + (q0 - c * ctx.npx) : ctx.p0;
+    const int e1 = !has1 ? e : ((sbits >> s) & 1u) ? e + 1 + (a.P - ctx.npx) : e + 1;
+    const unsigned b0 = 2u * (unsigned)e, b1 = 2u * (unsigned)e1;
+    r[2 * s] = __uint_as_float(al ? ld_u32(xg, b0) : (ld_u16(xg, b0) | (ld_u16(xg, b1) << 16)));
+  }
+  if (!bad) {
+    fbits = 0;
+#pragma unroll
+    for (int s = 0; s < NP; ++s) {
+      const int q0 = 2 * (tid + s * kBlock);
+      const bool in = q0 < ctx.nq, has1 = q0 + 1 < ctx.nq, split = (sbits >> s) & 1u;
+      const int pl = in ? q0 - plane_of(q0, ctx.npx) * ctx.npx : 0;
+      if (in && pixel_label(s_flag, a.C, ctx.npx, pl)) fbits |= 1u << (2 * s);
+      if (has1 && pixel_label(s_flag, a.C, ctx.npx, split || !has1 ? 0 : pl + 1)) fbits |= 2u << (2 * s);
+    }
+  }
 #pragma unroll
   for (int s = 0; s < NP; ++s) {
     const int q0 = 2 * (tid + s * kBlock);
-    if (q0 >= ctx.nq) continue;
-    const bool has1 = (vbits >> (2 * s + 1)) & 1u;
-    const bool split = (sbits >> s) & 1u;
-    const int c = q0 / ctx.npx;
-    const int pl = q0 - c * ctx.npx;
-    const int e = c * a.P + ctx.p0 + pl;
-    const int e1 = split ? e + 1 + (a.P - ctx.npx) : e + 1;
-    if (!bad) {
-      fbits &= ~(3u << (2 * s));
-      if (pixel_label(s_flag, a.C, ctx.npx, pl)) fbits |= 1u << (2 * s);
-      if (has1 && pixel_label(s_flag, a.C, ctx.npx, split ? 0 : pl + 1)) fbits |= 2u << (2 * s);
-    }
-    const unsigned b0 = 2u * (unsigned)e, b1 = 2u * (unsigned)e1;
-    uint32_t xw;
-    if (al) xw = ld_u32(xg, b0);
-    else xw = ld_u16(xg, b0) | (has1 ? (ld_u16(xg, b1) << 16) : 0u);
+    const uint32_t xw = __float_as_uint(r[2 * s]);
     float acc0 = bf_lo(xw), acc1 = bf_hi(xw);
 #pragma unroll
     for (int j = 0; j < K; ++j) {
       acc0 = fmaf(-bf_lo(u[s][j]), ks.yf[j], acc0);
       acc1 = fmaf(-bf_hi(u[s][j]), ks.yf[j], acc1);
     }
-    r[2 * s] = acc0;
-    r[2 * s + 1] = has1 ? acc1 : 0.f;
+    r[2 * s] = q0 < ctx.nq ? acc0 : 0.f;
+    r[2 * s + 1] = q0 + 1 < ctx.nq ? acc1 : 0.f;
   }
   }
   // the last frame stored nothing (rejected, or no step): store the updated tile
