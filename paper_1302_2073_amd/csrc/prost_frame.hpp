@@ -1306,7 +1306,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
   }
 #pragma unroll
   for (int s = 0; s < NR; ++s) {
-    if (past(s)) continue;
+    if (past(s)) break;
     const int q = tid + s * kBlock;
     const bool in = q < ctx.nq;
     const int c = plane_of(q, ctx.npx);
@@ -1329,7 +1329,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
   }
 #pragma unroll
   for (int s = 0; s < NR; ++s) {
-    if (past(s)) continue;
+    if (past(s)) break;
     const bool in = eix[s] >= 0;
     wt[s] = in ? (fgl[s] ? a.omega : 1.0f) : 0.f;
     float acc = r[s];
@@ -1357,7 +1357,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
     for (int j = 0; j <= K; ++j) acc[j] = 0.f;
 #pragma unroll
     for (int s = 0; s < NR; ++s) {
-      if (past(s)) continue;
+      if (past(s)) break;
       float phi, c;
       cost_eval(r[s], a.cp, phi, c);
       const float wc = wt[s] * c;
@@ -1386,7 +1386,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
       }
 #pragma unroll
       for (int s = 0; s < NR; ++s) {
-        if (past(s)) continue;
+        if (past(s)) break;
         float t = 0.f;
 #pragma unroll
         for (int j = 0; j < K; ++j) t = fmaf(u[s][j], ks.df[j], t);
@@ -1404,7 +1404,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
     float accb[1] = {0.f};
 #pragma unroll
     for (int s = 0; s < NR; ++s) {
-      if (past(s)) continue;
+      if (past(s)) break;
       float t = 0.f;
 #pragma unroll
       for (int j = 0; j < K; ++j) t = fmaf(u[s][j], ks.df[j], t);
@@ -1435,7 +1435,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
     if constexpr (EXT) acce[LE - 1] = pupd ? m2sum : 0.f;
 #pragma unroll
     for (int s = 0; s < NR; ++s) {
-      if (past(s)) continue;
+      if (past(s)) break;
       float phi, c;
       cost_eval(r[s], a.cp, phi, c);
       const float eta = -wt[s] * c * r[s];
@@ -1466,7 +1466,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
     if (SEQ && upd) u_pending = !store_u;
 #pragma unroll
     for (int s = 0; s < NR; ++s) {
-      if (past(s)) continue;
+      if (past(s)) break;
       const int q = tid + s * kBlock;
       if (eix[s] >= 0) {
         float rl = r[s];
@@ -1504,7 +1504,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
   if (!bad) {
 #pragma unroll
     for (int s = 0; s < NR; ++s) {
-      if (past(s)) continue;
+      if (past(s)) break;
       const int q = tid + s * kBlock;
       const int pl = eix[s] >= 0 ? q - plane_of(q, ctx.npx) * ctx.npx : 0;
       const float wn = pixel_label(s_flag, a.C, ctx.npx, pl) ? a.omega : 1.0f;
@@ -1513,7 +1513,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
   }
 #pragma unroll
   for (int s = 0; s < NR; ++s) {
-    if (past(s)) continue;
+    if (past(s)) break;
     float acc = r[s];
 #pragma unroll
     for (int j = 0; j < K; ++j) acc = fmaf(-u[s][j], ks.yf[j], acc);
