@@ -178,8 +178,8 @@ PROS_API pros_status pros_validate(const pros_params* prm);
  * MI355X at k = 15: up to 349 440 pixels x 3 channels in FP32 storage,
  * 698 880 in BF16) run the persistent frame kernel, U kept on chip for the
  * whole frame.  Larger frames run the streamed form: the same arithmetic,
- * one launch per dependent pass, U and the frame read from HBM in every
- * pass (pros_get_launch_info reports sync_mode -1); it has the default
+ * two launches per CG step, U and the frame read from HBM once in each and
+ * in the two passes after them (pros_get_launch_info reports sync_mode -1); it has the default
  * features only, so pre-processing (preprocess = 1) or the IRLS step
  * (ysolve = 2) with such a frame gives PROS_EUNSUPPORTED, before any
  * allocation, as does pros_set_score_output on a streamed handle. */
@@ -467,7 +467,7 @@ PROS_API pros_status pros_lpcost_bwd_noalloc(const float* U, const float* Y, con
  * tiles t = x mod 8; every workgroup reads the 8 group sums),
  * 3 = every workgroup reads all tagged partials (one hop, G^2 reads).
  * Results agree to float64 rounding.  rows_per_thread = -1 selects the
- * streamed form (one launch per pass, U read from HBM every pass; see
+ * streamed form (two launches per CG step, U read from HBM in each; see
  * pros_init) for any frame size; sync_mode is then ignored.
  * Synchronises. */
 PROS_API pros_status pros_set_launch(pros_handle* h, int32_t rows_per_thread, int32_t sync_mode);
