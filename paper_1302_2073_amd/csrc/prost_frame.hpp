@@ -1240,8 +1240,8 @@ __device__ __forceinline__ void tile_end(const FrameArgs& a, const int tile, KSp
 // dropped, so a tile is stored without a branch and a lane mask per entry (the
 // masks and the K base addresses did not fit the scalar registers: 1433 lane
 // reads for them in the k = 15 bfloat16 update).  640x480x3, k = 15, update pass:
-// 16 bfloat16 rows per thread 9.9 -> 5.1 us, 8 rows 6.5 -> 3.1, one frame's kernel
-// 55.6 -> 51.3; float32 160x120x3 2.8 -> 1.6.
+// 16 bfloat16 rows per thread 9.9 -> 5.7 us, 8 rows 6.5 -> 3.8, one frame's kernel
+// 55.6 -> 51.5; float32 160x120x3 2.8 -> 1.9.
 constexpr unsigned kNowhere = 0xFFFFFFF0u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t column_rows(void* col, int m, int entry_bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(col, 0, (unsigned)m * entry_bytes, 0x00027000);
@@ -1268,8 +1268,8 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
   int eix[NR];
   // Rows past the tile's end: a tile of 16 rows per thread is chosen for whatever
   // 8 do not hold, so its upper half is worked in pairs, up to the last one in use
-  // (80x60x1: 10 rows of 16, a frame with its mask 36 -> 33 us); a scalar compare
-  // per pair of rows.
+  // (80x60x1: 10 rows of 16, a frame with its mask 36 -> 32 us); a scalar compare
+  // and one exit per pair of rows.
   auto past = [&](int s) { return NR == 16 && s >= 8 && (s & ~1) * kBlock >= ctx.nq; };
   bool u_pending = false;   // sequence: the registers hold an update not yet stored
   auto store_tile = [&]() {  // sequence: the register tile to the U planes
@@ -1291,9 +1291,10 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
   float m2sum = 0.f;
   // Every load of the tile is asked for before any is used (a thread's rows one
   // after the other cost a memory latency each: to the first exchange 640x480x3,
-  // k = 15 10.5 -> 9.3 us, 160x120x3 4.4 -> 3.6, 80x60x1, k = 5 4.4 -> 3.7).  A row past the tile's end takes the first entry's
-  // values; its weight is 0 and it is never written.  32-bit byte offsets from
-  // uniform plane bases: a resident frame's planes are far below 4 GB.
+  // k = 15 10.5 -> 7.8 us, 160x120x3 4.4 -> 3.0, 80x60x1, k = 5 4.4 -> 3.7).  A row
+  // past the tile's end takes the first entry's values; its weight is 0 and it is
+  // never written.  32-bit byte offsets from uniform plane bases: a resident
+  // frame's planes are far below 4 GB.
   uint8_t fgl[NR];
   unsigned ub[NR];
 #pragma unroll
@@ -1610,7 +1611,7 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
   const float pinv_n = ks.pre_inv_n, pinv_s = ks.pre_inv_s;
   float m2sum = 0.f;
   // Loads first, as in the float32 tile (640x480x3, k = 15, 16 rows per thread:
-  // 14.3 -> 8.9 us to the first exchange; 8 rows 8.0 -> 5.9).  A pair past the
+  // 14.3 -> 7.0 us to the first exchange; 8 rows 8.0 -> 4.6).  A pair past the
   // tile's end takes the first entry's values.  The pairs held in LDS go before the
   // register pairs, while the registers are free.
   // byte offsets in 32 bits from uniform plane bases: the addresses are a
