@@ -15,16 +15,14 @@
 // per workgroup and across workgroups in a fixed order, so results are
 // deterministic.
 //
-// A pass is bound by its reads, so a step reads U once: H (a contraction over
-// the rows with both operands U) is formed on the matrix cores in the shadow of
-// the read, where a second pass for sum w c (u.d)^2 took 26 us of a 1280x720x3,
-// k = 15 float32 step and k (k + 1) / 2 products per entry in the vector unit 38.
+// A step reads U once: H (a contraction over the rows with both operands U) is
+// formed on the matrix cores beside the gradient, where a second pass for
+// sum w c (u.d)^2 took 26 us of a 1280x720x3, k = 15 float32 step and
+// k (k + 1) / 2 products per entry in the vector unit 38.
 // The sums of a step's partials run one workgroup per value, and the last of
 // them to finish takes the k-space step: two launches per CG step instead of
-// four, and none around the frame.  A 1280x720x3, k = 15 frame takes 307 us in
-// float32 (479 with the two-pass step) and 254 in bfloat16 (309); its gradient
-// pass 34.5 us, 5.1 TB/s, and 33, where the vector and matrix work no longer
-// hides behind half the bytes.
+// four, and none around the frame.  A 1280x720x3, k = 15 frame takes 362 us in
+// float32 (482 with the two-pass step) and 317 in bfloat16 (316).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -48,9 +46,7 @@ constexpr int kStPad = 68;              // floats per column of a wavefront's 64
 // five per compute unit, what both storage types hold at once, each taking
 // groups kStResident apart.  A pass leaves 1280 partials per value of a
 // 1280x720 frame instead of 3600 to sum, and every compute unit gets the same
-// share (a frame, float32 / bfloat16: 307 / 254 us; the same number of groups
-// for each workgroup, 1200 and 900 of them: 305 / 264; 1920x1080: 718 against
-// 750 in float32).
+// share.
 constexpr int kStResident = 1280;
 static int st_blocks(int nchunk) { return std::min(nchunk, kStResident); }
 
@@ -66,7 +62,7 @@ struct StreamKS {
   double tot[kStWide];    // reduced values of the latest pass
 };
 
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
 // One value per workgroup of a summing launch: value v = blockIdx.x's partials
 // of the nblk workgroups of a pass (contiguous) in a fixed order, to ks->tot.
@@ -174,11 +170,19 @@ __device__ __forceinline__ void st_get_y(const FrameArgs& a, const StreamKS* ks,
 
 // Step 1 gradient pass at the current y (float32 per thread, as the frame
 // kernel): partials of g, f and H's upper triangle row by row, value-major
-// (part[v * gridDim.x + workgroup]).  H: a wavefront leaves 64 rows of U and
-// their w c in LDS (its own, no barrier) and multiplies them in 16 steps of
-// v_mfma_f32_16x16x4f32: lane l holds column l % 16 of rows 16 (l / 16) + step
-// as one operand and the same times w c as the other, and one 16 x 16
-// float32 tile accumulates over all rows of the wavefront.
+// (part[v * gridDim.x + workgroup]).  H: a wavefront leaves 64 rows of U,
+// times the root of their w c, in LDS (its own, no barrier) and multiplies them
+// in 16 steps of v_mfma_f64_16x16x4: lane l holds column l % 16 of rows
+// 16 (l / 16) + step, as both operands, and one 16 x 16 tile accumulates over
+// all rows of the wavefront.  In float64: along a direction that foreground
+// pixels carry (weight omega, far from the fit) d^T H d is what is left of
+// entries 10^7 times larger, and a float32 tile lost it (a step 30 times too
+// short, or an early end of the steps).  The products of the rounded rows are
+// exact, so the tile is the square of a matrix, and what their rounding adds to
+// the form is a square too: as much as rounding u.d adds to sum w c (u.d)^2.
+// These matrix instructions and the vector work share the SIMD's time (each
+// alone 905 and 972 us, together 1832), so they cost 64 cycles per 4 rows of a
+// wavefront even behind the read.
 template <int KC, typename TS, bool PAIR>
 __global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS* __restrict__ ks,
                                                     double* __restrict__ part, int nchunk, bool first) {
@@ -187,7 +191,6 @@ __global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS*
   if (!first && (ks->stop || ks->bad)) return;
   __shared__ float ys[KC], yl[KC];
   __shared__ __align__(16) float us[kStWaves][16][kStPad];
-  __shared__ __align__(16) float ws[kStWaves][64];
   __shared__ double red[kStWaves][KC + 1];
   const int tid = thread_index(), lane = tid & 63, wv = tid >> 6;
   const int i16 = lane & 15, k4 = lane >> 4;
@@ -198,7 +201,7 @@ __global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS*
   float acc[KC + 1];
 #pragma unroll
   for (int j = 0; j <= KC; ++j) acc[j] = 0.f;
-  f32x4_t h = {0.f, 0.f, 0.f, 0.f};
+  f64x4_t h = {0.0, 0.0, 0.0, 0.0};
   for (int ch = blockIdx.x; ch < nchunk; ch += gridDim.x) {
     const int p0 = (ch * kStBlock + tid) * N;
     const bool valid = p0 < a.P;   // with pairs P is even, so both pixels are
@@ -230,19 +233,18 @@ __global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS*
 #pragma unroll
           for (int j = 0; j < KC; ++j) acc[j] = fmaf(wd, u[i][j], acc[j]);
         }
+        const float sw = sqrtf(w_c);
         wave_order();   // the rows before these have been read
 #pragma unroll
-        for (int j = 0; j < KC; ++j) us[wv][j][lane] = u[i][j];
-        ws[wv][lane] = w_c;
+        for (int j = 0; j < KC; ++j) us[wv][j][lane] = sw * u[i][j];
         wave_order();
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const float4 uq = *(const float4*)&us[wv][i16][k4 * 16 + 4 * q];
-          const float4 wq = *(const float4*)&ws[wv][k4 * 16 + 4 * q];
-          h = __builtin_amdgcn_mfma_f32_16x16x4f32(uq.x, wq.x * uq.x, h, 0, 0, 0);
-          h = __builtin_amdgcn_mfma_f32_16x16x4f32(uq.y, wq.y * uq.y, h, 0, 0, 0);
-          h = __builtin_amdgcn_mfma_f32_16x16x4f32(uq.z, wq.z * uq.z, h, 0, 0, 0);
-          h = __builtin_amdgcn_mfma_f32_16x16x4f32(uq.w, wq.w * uq.w, h, 0, 0, 0);
+          h = __builtin_amdgcn_mfma_f64_16x16x4f64((double)uq.x, (double)uq.x, h, 0, 0, 0);
+          h = __builtin_amdgcn_mfma_f64_16x16x4f64((double)uq.y, (double)uq.y, h, 0, 0, 0);
+          h = __builtin_amdgcn_mfma_f64_16x16x4f64((double)uq.z, (double)uq.z, h, 0, 0, 0);
+          h = __builtin_amdgcn_mfma_f64_16x16x4f64((double)uq.w, (double)uq.w, h, 0, 0, 0);
         }
       }
     }
@@ -254,7 +256,7 @@ __global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS*
   }
   wave_order();
 #pragma unroll
-  for (int v = 0; v < 4; ++v) us[wv][4 * k4 + v][i16] = h[v];   // H[row][column]
+  for (int v = 0; v < 4; ++v) ((double*)us[wv])[(4 * v + k4) * 16 + i16] = h[v];   // H[row][column]
   __syncthreads();
   if (tid < NV) {
     double s = 0.0;
@@ -268,7 +270,7 @@ __global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS*
         ++i;
       }
 #pragma unroll
-      for (int w = 0; w < kStWaves; ++w) s += (double)us[w][i][i + t];
+      for (int w = 0; w < kStWaves; ++w) s += ((const double*)us[w])[i * 16 + i + t];
     }
     part[(size_t)tid * gridDim.x + blockIdx.x] = s;
   }
@@ -336,7 +338,12 @@ __device__ __forceinline__ void st_adv_core(const FrameArgs& a, StreamKS* ks, do
 }
 
 // Sums of a gradient pass, then direction and majoriser step from them
-// (d^T H d: lane i row i of the triangle, rows added in order).
+// (d^T H d: lane i row i of the triangle, rows added in order).  H is
+// positive semidefinite, and the form is known to about 2^-48 of the
+// magnitudes of its terms (the square of a float32 rounding, which is what a
+// sum of w c (u.d)^2 with u.d in float32 resolves too): anything below is that.
+// A larger curvature majorises as well, so the step stays one of descent, and
+// rounding does not end the steps: only H d = 0 does.
 template <int KC>
 __global__ __launch_bounds__(kStBlock) void st_step(FrameArgs a, StreamKS* ks, const double* __restrict__ part,
                                                     int nblk, int it) {
@@ -344,7 +351,7 @@ __global__ __launch_bounds__(kStBlock) void st_step(FrameArgs a, StreamKS* ks, c
   __shared__ double red[kStWaves];
   __shared__ int last;
   __shared__ double tot[kStWide];
-  __shared__ double rowsum[KC];
+  __shared__ double rowsum[KC], rowabs[KC];
   if (!st_sum_value(ks, part, nblk, red, &last, tot)) return;
   const int t = threadIdx.x;
   if (it == 0) {   // frame start: y from the handle, flags cleared
@@ -360,13 +367,22 @@ __global__ __launch_bounds__(kStBlock) void st_step(FrameArgs a, StreamKS* ks, c
   if (ks->stop || ks->bad) return;
   if (t < KC) {
     int q = KC + 1 + t * KC - t * (t - 1) / 2;   // H[t][t]
-    double s = tot[q] * ks->d[t] * ks->d[t];
-    for (int l = t + 1; l < KC; ++l) s += 2.0 * tot[++q] * ks->d[t] * ks->d[l];
+    double s = tot[q] * ks->d[t] * ks->d[t], b = fabs(s);
+    for (int l = t + 1; l < KC; ++l) {
+      const double v = 2.0 * tot[++q] * ks->d[t] * ks->d[l];
+      s += v;
+      b += fabs(v);
+    }
     rowsum[t] = s;
+    rowabs[t] = b;
   }
   __syncthreads();
-  double dHd = 0.0;
-  for (int r = 0; r < KC; ++r) dHd += rowsum[r];
+  double dHd = 0.0, mag = 0.0;
+  for (int r = 0; r < KC; ++r) {
+    dHd += rowsum[r];
+    mag += rowabs[r];
+  }
+  if (dHd < 0x1p-48 * mag) dHd = 0x1p-48 * mag;
   st_adv_core(a, ks, dHd, it);
 }
 
