@@ -11,8 +11,9 @@
 // U^T eta, ||eta||^2 and the final cost), the geodesic scalars, and one pass
 // that updates U and labels every pixel (Step 3).  A thread takes one pixel
 // (all channels), or two adjacent ones in bfloat16 storage with even P and
-// aligned planes (32-bit accesses).  Reductions: float32 per thread, float64
-// per workgroup and across workgroups in a fixed order, so results are
+// aligned planes (32-bit accesses).  Reductions: float32 over the pixels that a
+// wavefront takes at a time, float64 over those and across wavefronts and
+// workgroups, H in float64 throughout; the order is fixed, so results are
 // deterministic.
 //
 // A step reads U once: H (a contraction over the rows with both operands U) is
@@ -21,8 +22,8 @@
 // k (k + 1) / 2 products per entry in the vector unit 38.
 // The sums of a step's partials run one workgroup per value, and the last of
 // them to finish takes the k-space step: two launches per CG step instead of
-// four, and none around the frame.  A 1280x720x3, k = 15 frame takes 362 us in
-// float32 (482 with the two-pass step) and 317 in bfloat16 (316).
+// four, and none around the frame.  A 1280x720x3, k = 15 frame takes 359 us in
+// float32 (482 with the two-pass step) and 309 in bfloat16 (315).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -182,30 +183,37 @@ __device__ __forceinline__ void st_get_y(const FrameArgs& a, const StreamKS* ks,
 // the form is a square too: as much as rounding u.d adds to sum w c (u.d)^2.
 // These matrix instructions and the vector work share the SIMD's time (each
 // alone 905 and 972 us, together 1832), so they cost 64 cycles per 4 rows of a
-// wavefront even behind the read.
+// wavefront even behind the read.  Below 16 columns the tile has room for r
+// beside U, and its column of products is g: no separate sums.  f, and g at 16
+// columns, are float32 over a thread's pixels of one group, as the frame kernel
+// has them over a tile, and float64 over the groups: a float32 sum over all of a
+// workgroup's groups would lose more with every group of a larger frame.
 template <int KC, typename TS, bool PAIR>
 __global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS* __restrict__ ks,
                                                     double* __restrict__ part, int nchunk, bool first) {
   constexpr int N = StPix<TS, PAIR>::N;
   constexpr int NV = st_nh<KC>();
+  constexpr bool kGradInTile = KC < 16;   // column KC of the tile is r
+  constexpr int LG = kGradInTile ? 1 : KC + 1;
   if (!first && (ks->stop || ks->bad)) return;
   __shared__ float ys[KC], yl[KC];
   __shared__ __align__(16) float us[kStWaves][16][kStPad];
-  __shared__ double red[kStWaves][KC + 1];
+  __shared__ double red[kStWaves][LG];
   const int tid = thread_index(), lane = tid & 63, wv = tid >> 6;
   const int i16 = lane & 15, k4 = lane >> 4;
   if (tid < KC) st_get_y(a, ks, first, tid, ys, yl);
 #pragma unroll
-  for (int j = KC; j < 16; ++j) us[wv][j][lane] = 0.f;
+  for (int j = KC + 1; j < 16; ++j) us[wv][j][lane] = 0.f;
   __syncthreads();
-  float acc[KC + 1];
-#pragma unroll
-  for (int j = 0; j <= KC; ++j) acc[j] = 0.f;
+  double sum = 0.0;   // f of this thread, or component comp of (g, f) of the wavefront
+  int comp = 0;
   f64x4_t h = {0.0, 0.0, 0.0, 0.0};
   for (int ch = blockIdx.x; ch < nchunk; ch += gridDim.x) {
     const int p0 = (ch * kStBlock + tid) * N;
     const bool valid = p0 < a.P;   // with pairs P is even, so both pixels are
-    float wt[N];
+    float wt[N], acc[LG];
+#pragma unroll
+    for (int j = 0; j < LG; ++j) acc[j] = 0.f;
 #pragma unroll
     for (int i = 0; i < N; ++i) wt[i] = valid ? st_weight(a, p0 + i) : 0.f;
     for (int c = 0; c < a.C; ++c) {
@@ -222,21 +230,24 @@ __global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS*
       }
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        float w_c = 0.f;
+        float sw = 0.f, r = 0.f;
         if (valid) {
-          const float r = st_residual<KC>(x[i], u[i], ys, yl);
+          r = st_residual<KC>(x[i], u[i], ys, yl);
           float phi, cc;
           cost_eval(r, a.cp, phi, cc);
-          w_c = wt[i] * cc;
-          const float wd = w_c * r;                 // w phi'(r)
-          acc[KC] = fmaf(wt[i], phi, acc[KC]);
+          const float w_c = wt[i] * cc;
+          acc[LG - 1] = fmaf(wt[i], phi, acc[LG - 1]);
+          if constexpr (!kGradInTile) {
+            const float wd = w_c * r;                 // w phi'(r)
 #pragma unroll
-          for (int j = 0; j < KC; ++j) acc[j] = fmaf(wd, u[i][j], acc[j]);
+            for (int j = 0; j < KC; ++j) acc[j] = fmaf(wd, u[i][j], acc[j]);
+          }
+          sw = sqrtf(w_c);
         }
-        const float sw = sqrtf(w_c);
         wave_order();   // the rows before these have been read
 #pragma unroll
         for (int j = 0; j < KC; ++j) us[wv][j][lane] = sw * u[i][j];
+        if constexpr (kGradInTile) us[wv][KC][lane] = sw * r;
         wave_order();
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -248,11 +259,16 @@ __global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS*
         }
       }
     }
+    if constexpr (kGradInTile)
+      sum += (double)acc[0];
+    else
+      sum += (double)wave_reduce_scatter<LG>(acc, comp);
   }
-  {
-    int comp;
-    const float v = wave_reduce_scatter<KC + 1>(acc, comp);
-    if (wave_rs_owner<KC + 1>(lane) && comp <= KC) red[wv][comp] = (double)v;
+  if constexpr (kGradInTile) {
+    sum = wave_sum(sum);
+    if (lane == 0) red[wv][0] = sum;
+  } else {
+    if (wave_rs_owner<LG>(lane) && comp < LG) red[wv][comp] = sum;
   }
   wave_order();
 #pragma unroll
@@ -260,14 +276,18 @@ __global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS*
   __syncthreads();
   if (tid < NV) {
     double s = 0.0;
-    if (tid <= KC) {
+    if (tid == KC || (!kGradInTile && tid < KC)) {
 #pragma unroll
-      for (int w = 0; w < kStWaves; ++w) s += red[w][tid];
+      for (int w = 0; w < kStWaves; ++w) s += red[w][kGradInTile ? 0 : tid];
     } else {
-      int i = 0, t = tid - (KC + 1);
-      while (t >= KC - i) {
-        t -= KC - i;
-        ++i;
+      int i = tid, t = KC - tid;   // g: row tid, column KC
+      if (tid > KC) {
+        i = 0;
+        t = tid - (KC + 1);
+        while (t >= KC - i) {
+          t -= KC - i;
+          ++i;
+        }
       }
 #pragma unroll
       for (int w = 0; w < kStWaves; ++w) s += ((const double*)us[w])[i * 16 + i + t];
@@ -387,7 +407,8 @@ __global__ __launch_bounds__(kStBlock) void st_step(FrameArgs a, StreamKS* ks, c
 }
 
 // Step 2 eta pass at the final y: eta = -w phi'(r) stored per entry;
-// partials of U^T eta, ||eta||^2 and the final cost.
+// partials of U^T eta, ||eta||^2 and the final cost: float32 over the pixels of
+// one group, float64 over the groups.
 template <int KC, typename TS, bool PAIR>
 __global__ __launch_bounds__(kStBlock) void st_eta(FrameArgs a, const StreamKS* __restrict__ ks, float* __restrict__ eta,
                                                    double* __restrict__ part, int nchunk) {
@@ -399,16 +420,17 @@ __global__ __launch_bounds__(kStBlock) void st_eta(FrameArgs a, const StreamKS* 
   const int tid = thread_index(), lane = tid & 63, wv = tid >> 6;
   if (tid < KC) st_get_y(a, ks, false, tid, ys, yl);
   __syncthreads();
-  float acc[L];
-#pragma unroll
-  for (int j = 0; j < L; ++j) acc[j] = 0.f;
+  double sum = 0.0;
+  int comp = 0;
   for (int ch = blockIdx.x; ch < nchunk; ch += gridDim.x) {
     const int p0 = (ch * kStBlock + tid) * N;
-    if (p0 >= a.P) continue;
-    float wt[N];
+    const bool valid = p0 < a.P;
+    float wt[N], acc[L];
 #pragma unroll
-    for (int i = 0; i < N; ++i) wt[i] = st_weight(a, p0 + i);
-    for (int c = 0; c < a.C; ++c) {
+    for (int j = 0; j < L; ++j) acc[j] = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) wt[i] = valid ? st_weight(a, p0 + i) : 0.f;
+    for (int c = 0; valid && c < a.C; ++c) {
       float u[N][KC], x[N];
       st_load<KC, TS, PAIR>(a, c, p0, u, x);
       const long long e = (long long)c * a.P + p0;
@@ -425,10 +447,9 @@ __global__ __launch_bounds__(kStBlock) void st_eta(FrameArgs a, const StreamKS* 
         for (int j = 0; j < KC; ++j) acc[j] = fmaf(et, u[i][j], acc[j]);
       }
     }
+    sum += (double)wave_reduce_scatter<L>(acc, comp);
   }
-  int comp;
-  const float v = wave_reduce_scatter<L>(acc, comp);
-  if (wave_rs_owner<L>(lane) && comp < L) red[wv][comp] = (double)v;
+  if (wave_rs_owner<L>(lane) && comp < L) red[wv][comp] = sum;
   __syncthreads();
   if (tid < L) {
     double s = 0.0;

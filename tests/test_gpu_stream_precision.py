@@ -1,5 +1,6 @@
-"""Precision of the streamed form's reductions: a CG step along a direction that only foreground pixels carry, whose
-curvature is what is left of entries millions of times larger."""
+"""Precision of the streamed form's reductions: a CG step along a direction that only foreground pixels carry (the
+curvature is what is left of entries millions of times larger), and sums whose terms cancel over the pixel groups of a
+workgroup."""
 import numpy as np
 import pytest
 
@@ -63,3 +64,23 @@ def test_step_along_a_direction_of_foreground_pixels(width, height, channels, k,
     assert np.isclose(s["alpha"][0], info.cg.alpha[0], rtol=TOL_STEP, atol=0)
     assert np.allclose(s["f"], info.cg.f, rtol=TOL_F, atol=0)
     assert np.linalg.norm(y - new.y) <= TOL_Y * np.linalg.norm(new.y)
+
+
+@pytest.mark.parametrize("k", [1, 16])
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_sums_over_many_pixel_groups(storage, k):
+    """p = 2 and one constant column (the others 0): y is the mean of x over u, with x = 2^13 in the first third of the
+    pixels, 2^-13 in the second and -2^13 in the last.  All products are powers of two, so a group's sums are exact,
+    and the thirds are groups apart: a float32 sum over a workgroup's groups loses the second third altogether."""
+    from paper_1302_2073_amd.tracker import Tracker
+    width, height = 1280, 1536
+    P = width * height
+    U = np.zeros((P, k))
+    U[:, 0] = 2.0 ** -10
+    x = np.repeat([2.0 ** 13, 2.0 ** -13, -2.0 ** 13], P // 3)
+    with Tracker(width, height, 1, k, storage=storage, cg_iters=1, p=2.0, mu=1e-3, delta=0.1) as t:
+        t.set_launch(-1)
+        t.set_state(U, np.zeros(k), None, 150)
+        t.track(_tensor(x, storage))
+        y = t.get_state()[1]
+    assert np.isclose(y[0], 2.0 ** -3 / 3, rtol=TOL_F, atol=0)
