@@ -165,10 +165,7 @@ __global__ __launch_bounds__(kSolveThreads) void gram_solve(const double* __rest
     }
     off = wave_sum(off);
     dia = wave_sum(dia);
-    // what is left is rounding of the rotations themselves (entries near
-    // 2^-53 of the diagonal): a tighter bound is not reached when U is
-    // orthonormal already, and all 30 sweeps would run
-    if (!(off > 1e-30 * dia)) break;
+    if (!(off > 1e-32 * dia)) break;
     for (int s = 0; s < n - 1; ++s) {
       // pair i of step s: (n - 1, s) for i = 0, ((s + i) mod (n - 1), (s - i) mod (n - 1)) else
       auto first = [&](int i) { return i == 0 ? n - 1 : s + i >= n - 1 ? s + i - (n - 1) : s + i; };
@@ -192,9 +189,12 @@ __global__ __launch_bounds__(kSolveThreads) void gram_solve(const double* __rest
         const double a = A[p][u], b = A[p][v], c = A[q][u], d = A[q][v];
         const double a1 = cj * a - sj * b, b1 = sj * a + cj * b;
         const double c1 = cj * c - sj * d, d1 = sj * c + cj * d;
+        // a pair's own off-diagonal is 0 by the choice of its angle; as computed it
+        // would keep rounding of the diagonal (2^-53 of it), above the bound of the
+        // sweeps, all 30 of which would then run
         A[p][u] = ci * a1 - si * c1;
-        A[p][v] = ci * b1 - si * d1;
-        A[q][u] = si * a1 + ci * c1;
+        A[p][v] = bi == bj ? 0.0 : ci * b1 - si * d1;
+        A[q][u] = bi == bj ? 0.0 : si * a1 + ci * c1;
         A[q][v] = si * b1 + ci * d1;
       }
 #pragma unroll
