@@ -174,8 +174,11 @@ __global__ __launch_bounds__(kSolveThreads) void gram_solve(const double* __rest
         const int p = first(l), q = second(l);
         const double apq = A[p][q], th = A[q][q] - A[p][p], d = 2.0 * apq;
         double c = 1.0, sn = 0.0;
-        if (apq != 0.0) {   // t = sgn(tau) / (|tau| + sqrt(1 + tau^2)), tau = th / d
-          const double t = (th >= 0.0 ? d : -d) / (fabs(th) + sqrt(fma(th, th, d * d)));
+        const double den = fabs(th) + sqrt(fma(th, th, d * d));
+        // den is 0 where th is 0 and d^2 underflows (|apq| below 2^-538): as good as
+        // rotated, and 0 / 0 would spoil the whole decomposition
+        if (apq != 0.0 && den > 0.0) {   // t = sgn(tau) / (|tau| + sqrt(1 + tau^2)), tau = th / d
+          const double t = (th >= 0.0 ? d : -d) / den;
           c = rsqrt(fma(t, t, 1.0));
           sn = t * c;
         }
