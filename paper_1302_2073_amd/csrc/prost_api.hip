@@ -447,7 +447,7 @@ pros_status prost_host::create_handle(const pros_params* prm, hipStream_t stream
   int wclk_khz = 0;
   INIT_TRY(hipDeviceGetAttribute(&wclk_khz, hipDeviceAttributeWallClockRate, h->device));
   if (wclk_khz <= 0) wclk_khz = 100000;
-  h->timeout_ticks = (long long)wclk_khz * 1000LL * 2;  // 2 s per barrier wait
+  h->timeout_ticks = (long long)wclk_khz * 1000LL * 2;  // 2 s per exchange or barrier wait
   if (g_force > 0) {             // launch owned by a batch
     h->NR = nr_force;
     h->tpw = tpw_force;

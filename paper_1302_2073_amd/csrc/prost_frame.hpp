@@ -257,21 +257,30 @@ __device__ __forceinline__ void wave_order() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// The waits of an exchange: one clock for all of its gathers, slots and
+// components, read where the exchange begins: its latency is behind the
+// workgroup's own sums there.  A frame takes 0.5 us more with it than with a
+// clock for every value (160x120x3 to 640x480x3), 0.6 with the read next to the
+// gather, 1.2 with one that the first missing value starts.
+struct GangWait {
+  long long t0;
+  int bad;   // gave up
+};
+
 // Waits for *p to carry epoch ep, x being what a load of it returned; the
-// value without its tag, or 0 with `bad` set after a time-out.
-__device__ __forceinline__ double wait_tagged(const double* p, double x, unsigned ep, const FrameArgs& a, int& bad) {
-  if (tag_of(x) != ep) {
-    const long long t0 = now_ticks();
-    unsigned spins = 0;
-    do {
-      x = ld_tagged(p);
-      if ((++spins & 63u) == 0 &&
-          (now_ticks() - t0 > a.timeout ||
-           (__hip_atomic_load(&a.sync[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kErrTimeout))) {
-        bad = 1;
-        return 0.0;
-      }
-    } while (tag_of(x) != ep);
+// value without its tag, or 0 with w.bad set after the time-out (what is still
+// missing then costs 64 polls each).
+__device__ __forceinline__ double wait_tagged(const double* p, double x, unsigned ep, const FrameArgs& a,
+                                              GangWait& w) {
+  unsigned spins = 0;
+  while (tag_of(x) != ep) {
+    x = ld_tagged(p);
+    if ((++spins & 63u) == 0 &&
+        (now_ticks() - w.t0 > a.timeout ||
+         (__hip_atomic_load(&a.sync[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kErrTimeout))) {
+      w.bad = 1;
+      return 0.0;
+    }
   }
   return untag(x);
 }
@@ -281,7 +290,7 @@ __device__ __forceinline__ double wait_tagged(const double* p, double x, unsigne
 // v, and component 16 + comp, if there is one, into vx.
 template <int L>
 __device__ __forceinline__ void poll_pair(const double* base, int n, size_t qstride, int q0, int dq, int comp,
-                                          unsigned ep, const FrameArgs& a, double& v, double& vx, int& bad) {
+                                          unsigned ep, const FrameArgs& a, double& v, double& vx, GangWait& w) {
   const double* p0 = base + (size_t)q0 * qstride + comp;
   const double* p1 = p0 + (size_t)dq * qstride;
   const bool on0 = comp < L && q0 < n, on1 = comp < L && q0 + dq < n;
@@ -291,16 +300,23 @@ __device__ __forceinline__ void poll_pair(const double* base, int n, size_t qstr
   if (on1) x1 = ld_tagged(p1);
   if (L > 16 && ex0) e0 = ld_tagged(p0 + 16);
   if (L > 16 && ex1) e1 = ld_tagged(p1 + 16);
-  if (on0) v += wait_tagged(p0, x0, ep, a, bad);
-  if (on1) v += wait_tagged(p1, x1, ep, a, bad);
-  if (L > 16 && ex0) vx += wait_tagged(p0 + 16, e0, ep, a, bad);
-  if (L > 16 && ex1) vx += wait_tagged(p1 + 16, e1, ep, a, bad);
+  if (on0) v += wait_tagged(p0, x0, ep, a, w);
+  if (on1) v += wait_tagged(p1, x1, ep, a, w);
+  if (L > 16 && ex0) vx += wait_tagged(p0 + 16, e0, ep, a, w);
+  if (L > 16 && ex1) vx += wait_tagged(p1 + 16, e1, ep, a, w);
+}
+
+// Sum of the slots q0, q0 + dq, q0 + 2 dq, ... below n, two at a time.
+template <int L>
+__device__ __forceinline__ void poll_slots(const double* base, int n, size_t qstride, int q0, int dq, int comp,
+                                           unsigned ep, const FrameArgs& a, double& v, double& vx, GangWait& w) {
+  for (int q = q0; q < n; q += 2 * dq) poll_pair<L>(base, n, qstride, q, dq, comp, ep, a, v, vx, w);
 }
 
 // Raises the gang's time-out bit and the workgroup's flag if a lane of this
 // wavefront gave up.
-__device__ __forceinline__ void wave_give_up(int bad, const FrameArgs& a, FrameSmem& sm) {
-  if (__any(bad) && (thread_index() & 63) == 0) {
+__device__ __forceinline__ void wave_give_up(const GangWait& w, const FrameArgs& a, FrameSmem& sm) {
+  if (__any(w.bad) && (thread_index() & 63) == 0) {
     sm.ctl[2] = 1;
     __hip_atomic_fetch_or(&a.sync[2], kErrTimeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -315,21 +331,20 @@ __device__ __forceinline__ void wave_give_up(int bad, const FrameArgs& a, FrameS
 // barrier that also reduces a predicate takes 0.2 us more).
 template <int L>
 __device__ __forceinline__ void gather_slots(const double* base, int n, size_t qstride, unsigned ep,
-                                             const FrameArgs& a, FrameSmem& sm) {
+                                             const FrameArgs& a, FrameSmem& sm, long long t0) {
   const int lane = thread_index() & 63, wv = thread_index() >> 6;
   const int comp = lane & 15;
   constexpr int kRows = 4 * kWaves;
   double v = 0.0, vx = 0.0;
-  int bad = 0;
-  for (int q = 4 * wv + (lane >> 4); q < n; q += 2 * kRows)
-    poll_pair<L>(base, n, qstride, q, kRows, comp, ep, a, v, vx, bad);
+  GangWait w{t0, 0};
+  poll_slots<L>(base, n, qstride, 4 * wv + (lane >> 4), kRows, comp, ep, a, v, vx, w);
   v = swap_sum<16>(swap_sum<32>(v));
   if (L > 16) vx = swap_sum<16>(swap_sum<32>(vx));
   if (lane < 16) {
     sm.got[wv][comp] = v;
     if (16 + comp < L) sm.got[wv][16 + comp] = vx;
   }
-  wave_give_up(bad, a, sm);
+  wave_give_up(w, a, sm);
   __syncthreads();
 }
 
@@ -366,6 +381,7 @@ __device__ __forceinline__ void gang_reduce_wave0(float (&acc)[L], const FrameAr
                                                   unsigned ebase, FrameSmem& sm, double* s_out) {
   constexpr int LM = L - LATE;
   const int tid = thread_index(), lane = tid & 63, wv = tid >> 6;
+  const long long t0 = now_ticks();
   {
     int comp;
     const float v = wave_reduce_scatter<L>(acc, comp);
@@ -392,7 +408,7 @@ __device__ __forceinline__ void gang_reduce_wave0(float (&acc)[L], const FrameAr
   trace_point(a, tile, 24 + 3 * nbar);
   const int comp = lane & 15;
   if (a.sync_mode == 3) {
-    gather_slots<LM>(slots, a.G, kSlot, ep, a, sm);
+    gather_slots<LM>(slots, a.G, kSlot, ep, a, sm, t0);
     if (tid < LM) {
       double v = 0.0;
 #pragma unroll
@@ -404,7 +420,7 @@ __device__ __forceinline__ void gang_reduce_wave0(float (&acc)[L], const FrameAr
     double* gs = a.part + (size_t)(2 * a.G + set * kGroups * kReplicas) * kSlot;   // [copy][group]
     if (tile < kGroups) {   // group leader: members tile, tile + 8, ...
       const int n = (a.G - tile + kGroups - 1) / kGroups;
-      gather_slots<LM>(slots + (size_t)tile * kSlot, n, (size_t)kGroups * kSlot, ep, a, sm);
+      gather_slots<LM>(slots + (size_t)tile * kSlot, n, (size_t)kGroups * kSlot, ep, a, sm, t0);
       if (wv == 0 && sm.ctl[2] == 0) {
         double v = 0.0, vx = 0.0;
 #pragma unroll
@@ -422,29 +438,29 @@ __device__ __forceinline__ void gang_reduce_wave0(float (&acc)[L], const FrameAr
     }
     if (wv == 0) {
       double v = 0.0, vx = 0.0;
-      int bad = 0;
+      GangWait w{t0, 0};
       poll_pair<LM>(gs + (size_t)(tile & (kReplicas - 1)) * kGroups * kSlot, min(kGroups, a.G), kSlot, lane >> 4, 4,
-                    comp, ep, a, v, vx, bad);
+                    comp, ep, a, v, vx, w);
       v = swap_sum<16>(swap_sum<32>(v));
       if (LM > 16) vx = swap_sum<16>(swap_sum<32>(vx));
       if (lane < 16) {
         if (comp < LM) s_out[comp] = v;
         if (16 + comp < LM) s_out[16 + comp] = vx;
       }
-      wave_give_up(bad, a, sm);
+      wave_give_up(w, a, sm);
       wave_order();
     }
   }
   if (LATE > 0 && tile == 0 && wv == 1) {
-    int bad = 0;
+    GangWait w{t0, 0};
 #pragma unroll
     for (int c = LM; c < L; ++c) {
       double v = 0.0, none = 0.0;
-      for (int q = lane; q < a.G; q += 128) poll_pair<1>(slots + c, a.G, kSlot, q, 64, 0, ep, a, v, none, bad);
+      poll_slots<1>(slots + c, a.G, kSlot, lane, 64, 0, ep, a, v, none, w);
       v = wave_sum(v);
       if (lane == 0) s_out[c] = v;
     }
-    wave_give_up(bad, a, sm);
+    wave_give_up(w, a, sm);
   }
 }
 
@@ -457,6 +473,7 @@ template <typename IDLE>
 __device__ __forceinline__ bool gang_reduce_one(float acc, const FrameArgs& a, const int tile, int& nbar,
                                                 unsigned ebase, FrameSmem& sm, double& total, IDLE idle) {
   const int tid = thread_index(), lane = tid & 63;
+  const long long t0 = now_ticks();
   {
     float v[1] = {acc};
     int comp;
@@ -479,31 +496,30 @@ __device__ __forceinline__ bool gang_reduce_one(float acc, const FrameArgs& a, c
   if (tid < 64) {
     const int set = slot_set(a, ep);
     double* slots = a.part + (size_t)(a.sync_mode == 3 && set ? a.G : 0) * kSlot;
-    int bad = 0;
+    GangWait w{t0, 0};
     if (lane == 0) st_tagged(slots + (size_t)tile * kSlot, tag_value(v, ep));
     v = 0.0;
     double none = 0.0;
     if (a.sync_mode == 3) {
-      for (int q = lane; q < a.G; q += 128) poll_pair<1>(slots, a.G, kSlot, q, 64, 0, ep, a, v, none, bad);
+      poll_slots<1>(slots, a.G, kSlot, lane, 64, 0, ep, a, v, none, w);
     } else {
       double* gs = a.part + (size_t)(2 * a.G + set * kGroups * kReplicas) * kSlot;
       if (tile < kGroups) {
         const int n = (a.G - tile + kGroups - 1) / kGroups;
-        for (int q = lane; q < n; q += 128)
-          poll_pair<1>(slots + (size_t)tile * kSlot, n, (size_t)kGroups * kSlot, q, 64, 0, ep, a, v, none, bad);
+        poll_slots<1>(slots + (size_t)tile * kSlot, n, (size_t)kGroups * kSlot, lane, 64, 0, ep, a, v, none, w);
         v = wave_sum(v);
-        if (!__any(bad) && lane < kReplicas) st_tagged(gs + (size_t)(lane * kGroups + tile) * kSlot, tag_value(v, ep));
+        if (!__any(w.bad) && lane < kReplicas) st_tagged(gs + (size_t)(lane * kGroups + tile) * kSlot, tag_value(v, ep));
         trace_point(a, tile, 25 + 3 * (nbar - 1));
         v = 0.0;
       }
-      if (!__any(bad) && lane < min(kGroups, a.G)) {
+      if (!__any(w.bad) && lane < min(kGroups, a.G)) {
         const double* p = gs + (size_t)((tile & (kReplicas - 1)) * kGroups + lane) * kSlot;
-        v = wait_tagged(p, ld_tagged(p), ep, a, bad);
+        v = wait_tagged(p, ld_tagged(p), ep, a, w);
       }
     }
     v = wave_sum(v);
     if (lane == 0) sm.one = v;
-    wave_give_up(bad, a, sm);
+    wave_give_up(w, a, sm);
   } else {
     idle();
   }
