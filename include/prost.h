@@ -468,7 +468,9 @@ PROS_API pros_status pros_lpcost_bwd_noalloc(const float* U, const float* Y, con
  * 3 = every workgroup reads all tagged partials (one hop, G^2 reads).
  * Results agree to float64 rounding.  rows_per_thread = -1 selects the
  * streamed form (two launches per CG step, U read from HBM in each; see
- * pros_init) for any frame size; sync_mode is then ignored.
+ * pros_init) for any frame size; sync_mode is then ignored.  A bfloat16
+ * handle with curvature schedule 1 stays streamed (PROS_EUNSUPPORTED for a
+ * tile; see pros_set_curvature).  A refused call changes nothing.
  * Synchronises. */
 PROS_API pros_status pros_set_launch(pros_handle* h, int32_t rows_per_thread, int32_t sync_mode);
 

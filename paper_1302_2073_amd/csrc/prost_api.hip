@@ -343,7 +343,7 @@ bool prost_host::pair_layout(const pros_handle* h) {
 // memory round trip).  Frames too large for one workgroup per CU take the
 // largest tile that is resident.  force_nr > 0 asks for one row count.
 constexpr int kSmallGang = 32;
-static pros_status choose_launch(pros_handle* h, int force_nr) {
+static pros_status pick_launch(pros_handle* h, int force_nr) {
   const int nrs[] = {1, 2, 4, 8, 16, 32};
   const void* best = nullptr;
   int bestNR = 0, bestG = 0, bestT = 0;
@@ -419,6 +419,42 @@ static pros_status choose_launch(pros_handle* h, int force_nr) {
   return PROS_OK;
 }
 
+// The launch of a handle whose tile (force_nr) or features have changed; what is
+// refused leaves it as it was.  Schedule 1 is taken by streamed handles of either
+// storage type, but the tile kernels that reduce H are float32.
+static pros_status choose_launch(pros_handle* h, int force_nr) {
+  const bool streamed = h->streamed;
+  const void* kfn = h->kfn;
+  const int NR = h->NR, G = h->G, tpw = h->tpw;
+  pros_status st = pick_launch(h, force_nr);
+  if (st == PROS_OK && !h->streamed && h->curv == 1 && h->prm.storage != PROS_F32)
+    st = fail(PROS_EUNSUPPORTED, "curvature schedule 1 needs float32 storage (or the streamed form)");
+  if (st != PROS_OK) {
+    h->streamed = streamed;
+    h->kfn = kfn;
+    h->NR = NR;
+    h->G = G;
+    h->tpw = tpw;
+  }
+  return st;
+}
+
+pros_status prost_host::fit_part(pros_handle* h) {
+  const size_t need = part_bytes(h, h->G);
+  if (need <= h->part_cap) return PROS_OK;
+  (void)hipFree(h->part);
+  h->part = nullptr;
+  h->part_cap = 0;
+  hipError_t e = hipMalloc((void**)&h->part, need);
+  if (e != hipSuccess) {
+    h->broken = true;
+    h->broken_status = PROS_ENOMEM;
+    return fail(PROS_ENOMEM, "partials: %s", hipGetErrorString(e));
+  }
+  h->part_cap = need;
+  return PROS_OK;
+}
+
 pros_status prost_host::create_handle(const pros_params* prm, hipStream_t stream, int nr_force, int tpw_force,
                                       int g_force, pros_handle** out) {
   *out = nullptr;
@@ -469,6 +505,7 @@ pros_status prost_host::create_handle(const pros_params* prm, hipStream_t stream
   INIT_TRY(hipMalloc((void**)&h->stats, sizeof(pros_stats)));
   INIT_TRY(hipMalloc((void**)&h->seq, sizeof(void*) * kSeqChunk));
   INIT_TRY(hipMalloc((void**)&h->part, prost_host::part_bytes(h, h->G)));
+  h->part_cap = prost_host::part_bytes(h, h->G);
   INIT_TRY(hipMalloc((void**)&h->sync, 64));
   INIT_TRY(hipHostMalloc((void**)&h->pin, kPinHeader + (size_t)h->P, hipHostMallocDefault));
   INIT_TRY(hipMemsetAsync(h->U, 0, es * (size_t)h->ldU * h->k, h->stream));
@@ -937,19 +974,9 @@ pros_status pros_set_launch(pros_handle* h, int32_t rows_per_thread, int32_t syn
       rows_per_thread != 8 && rows_per_thread != 16 && rows_per_thread != 32)
     return fail(PROS_EINVAL, "rows_per_thread must be 0 (automatic), 1, 2, 4, 8, 16 or 32");
   HIP_TRY(hipStreamSynchronize(h->stream));
-  const int oldG = h->G;
   st = choose_launch(h, rows_per_thread);
+  if (st == PROS_OK) st = fit_part(h);   // the curvature schedule may have changed since, too
   if (st != PROS_OK) return st;
-  if (h->G > oldG) {
-    (void)hipFree(h->part);
-    h->part = nullptr;
-    hipError_t e = hipMalloc((void**)&h->part, prost_host::part_bytes(h, h->G));
-    if (e != hipSuccess) {
-      h->broken = true;
-      h->broken_status = PROS_ENOMEM;
-      return fail(PROS_ENOMEM, "partials: %s", hipGetErrorString(e));
-    }
-  }
   h->sync_mode = sync_mode;
   return prost_host::reset_exchange(h);
 }
@@ -983,14 +1010,8 @@ pros_status pros_set_curvature(pros_handle* h, int32_t schedule) {
     h->curv = old;
     return st;
   }
-  (void)hipFree(h->part);        // the wide exchange has its own slots
-  h->part = nullptr;
-  hipError_t e = hipMalloc((void**)&h->part, prost_host::part_bytes(h, h->G));
-  if (e != hipSuccess) {
-    h->broken = true;
-    h->broken_status = PROS_ENOMEM;
-    return fail(PROS_ENOMEM, "partials: %s", hipGetErrorString(e));
-  }
+  st = fit_part(h);              // the wide exchange has its own slots
+  if (st != PROS_OK) return st;
   return prost_host::reset_exchange(h);
 }
 

@@ -217,17 +217,12 @@ static pros_status configure(pros_batch* b, int budget, int wg_per_cu, double ti
     const int G = (h->P + tpw - 1) / tpw;
     if (G > nwg) return fail(PROS_EUNSUPPORTED, "a %dx%dx%d stream at k=%d needs %d workgroups (> %d)",
                              h->prm.width, h->prm.height, h->C, h->k, G, nwg);
-    if (G != h->G) {   // partial buffer sized by the gang
-      (void)hipFree(h->part);
-      h->part = nullptr;
-      e = hipMalloc((void**)&h->part, prost_host::part_bytes(h, G));
-      if (e != hipSuccess) return fail(PROS_ENOMEM, "partials: %s", hipGetErrorString(e));
-    }
     h->NR = NR;
     h->tpw = tpw;
     h->G = G;
     h->sync_mode = sync_mode;
-    pros_status rs = prost_host::reset_exchange(h);
+    pros_status rs = prost_host::fit_part(h);
+    if (rs == PROS_OK) rs = prost_host::reset_exchange(h);
     if (rs != PROS_OK) return rs;
   }
   b->budget = budget;

@@ -22,7 +22,8 @@ struct pros_handle {
   double* y = nullptr;
   long long* nframe = nullptr;
   pros_stats* stats = nullptr;
-  double* part = nullptr;
+  double* part = nullptr;       // exchange slots, part_cap bytes
+  size_t part_cap = 0;
   unsigned* sync = nullptr;
   void* reorth_ws = nullptr;
   float* pre_mean = nullptr;    // pre-processing: running average (m), or NULL
@@ -82,6 +83,9 @@ bool pair_layout(const pros_handle* h);
 // Bytes of the exchange buffer for a gang of G workgroups: the regular
 // slots, plus the wide region of the IRLS step when the stream uses it.
 size_t part_bytes(const pros_handle* h, int G);
+// The exchange buffer holds what the handle's gang and curvature schedule need
+// (a larger one is allocated; the handle is unusable if that fails).
+pros_status fit_part(pros_handle* h);
 
 uint16_t bf16_rne(float f);
 float bf16_to_f32(uint16_t b);
