@@ -183,9 +183,12 @@ __device__ __forceinline__ void st_get_y(const FrameArgs& a, const StreamKS* ks,
 // the form is a square too: as much as rounding u.d adds to sum w c (u.d)^2.
 // These matrix instructions and the vector work share the SIMD's time (each
 // alone 905 and 972 us, together 1832), so they cost 64 cycles per 4 rows of a
-// wavefront even behind the read.  Below 16 columns the tile has room for r
-// beside U, and its column of products is g: no separate sums.  f, and g at 16
-// columns, are float32 over a thread's pixels of one group, as the frame kernel
+// wavefront even behind the read.  Up to 8 columns two groups of 32 rows lie
+// side by side in the tile, up to 4 four of 16 (their products with each other
+// are not used): half and a quarter of the steps.  Below 16 columns the tile has
+// room for r beside U, and its column of products is g: no separate sums (at 8,
+// where r would take the second group's room, they cost less than it).  f, and g
+// where it is not in the tile, are float32 over a thread's pixels of one group, as the frame kernel
 // has them over a tile, and float64 over the groups: a float32 sum over all of a
 // workgroup's groups would lose more with every group of a larger frame.
 template <int KC, typename TS, bool PAIR>
@@ -193,17 +196,21 @@ __global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS*
                                                     double* __restrict__ part, int nchunk, bool first) {
   constexpr int N = StPix<TS, PAIR>::N;
   constexpr int NV = st_nh<KC>();
-  constexpr bool kGradInTile = KC < 16;   // column KC of the tile is r
+  constexpr bool kGradInTile = KC != 8 && KC < 16;   // column KC of the tile is r
   constexpr int LG = kGradInTile ? 1 : KC + 1;
+  constexpr int kCols = kGradInTile ? KC + 1 : KC;
+  constexpr int PK = kCols <= 4 ? 4 : kCols <= 8 ? 2 : 1;   // row groups side by side in the tile
+  constexpr int GC = 16 / PK, GR = 64 / PK;                 // columns and rows of a group
   if (!first && (ks->stop || ks->bad)) return;
   __shared__ float ys[KC], yl[KC];
   __shared__ __align__(16) float us[kStWaves][16][kStPad];
   __shared__ double red[kStWaves][LG];
   const int tid = thread_index(), lane = tid & 63, wv = tid >> 6;
   const int i16 = lane & 15, k4 = lane >> 4;
+  float (*const row)[kStPad] = &us[wv][lane / GR * GC];   // this lane's row: row[column][lane % GR]
   if (tid < KC) st_get_y(a, ks, first, tid, ys, yl);
 #pragma unroll
-  for (int j = KC + 1; j < 16; ++j) us[wv][j][lane] = 0.f;
+  for (int j = kCols; j < GC; ++j) row[j][lane % GR] = 0.f;
   __syncthreads();
   double sum = 0.0;   // f of this thread, or component comp of (g, f) of the wavefront
   int comp = 0;
@@ -246,12 +253,12 @@ __global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS*
         }
         wave_order();   // the rows before these have been read
 #pragma unroll
-        for (int j = 0; j < KC; ++j) us[wv][j][lane] = sw * u[i][j];
-        if constexpr (kGradInTile) us[wv][KC][lane] = sw * r;
+        for (int j = 0; j < KC; ++j) row[j][lane % GR] = sw * u[i][j];
+        if constexpr (kGradInTile) row[KC][lane % GR] = sw * r;
         wave_order();
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float4 uq = *(const float4*)&us[wv][i16][k4 * 16 + 4 * q];
+        for (int q = 0; q < GR / 16; ++q) {
+          const float4 uq = *(const float4*)&us[wv][i16][k4 * (GR / 4) + 4 * q];
           h = __builtin_amdgcn_mfma_f64_16x16x4f64((double)uq.x, (double)uq.x, h, 0, 0, 0);
           h = __builtin_amdgcn_mfma_f64_16x16x4f64((double)uq.y, (double)uq.y, h, 0, 0, 0);
           h = __builtin_amdgcn_mfma_f64_16x16x4f64((double)uq.z, (double)uq.z, h, 0, 0, 0);
@@ -290,7 +297,10 @@ __global__ __launch_bounds__(kStBlock) void st_grad(FrameArgs a, const StreamKS*
         }
       }
 #pragma unroll
-      for (int w = 0; w < kStWaves; ++w) s += ((const double*)us[w])[i * 16 + i + t];
+      for (int w = 0; w < kStWaves; ++w) {
+#pragma unroll
+        for (int p = 0; p < PK; ++p) s += ((const double*)us[w])[(p * GC + i) * 16 + p * GC + i + t];
+      }
     }
     part[(size_t)tid * gridDim.x + blockIdx.x] = s;
   }
