@@ -142,8 +142,8 @@ def run_plain(storage, steps, warmup, pool, curvature=0, cooperative=1):
 
 def run_streamed(storage, steps, warmup, pool=4, width=1280, height=720, curvature=None):
     """One stream of frames beyond the resident register tiles (1280x720x3,
-    k = 15): the streamed form, one launch per dependent pass (curvature:
-    the CG curvature schedule, None = the handle's default)."""
+    k = 15): the streamed form, two launches per CG step (curvature: the CG
+    curvature schedule, None = the handle's default; both run the same pass)."""
     import torch
     from paper_1302_2073_amd import Tracker
     from synth import video as V
@@ -719,8 +719,8 @@ def main():
                 try:
                     forms[name] = run_streamed(storage, max(args.steps // 4, 10), min(args.warmup, 5),
                                                curvature=curv)
-                    forms[name]["note"] = ("frames beyond the resident register tiles: one launch per dependent "
-                                           "pass, U and x read from HBM in every pass")
+                    forms[name]["note"] = ("frames beyond the resident register tiles: two launches per CG step, "
+                                           "U and x read from HBM once in each step and in the two passes after")
                 except Exception as exc:
                     forms[name] = {"error": repr(exc)[:300]}
     if "plain_f32_curv1" in want:

@@ -284,8 +284,10 @@ PROS_API pros_status pros_reorthonormalize(pros_handle* h);
 
 /* Launch configuration chosen for the handle (for diagnostics).  A
  * streamed handle reports sync_mode -1, rows_per_thread 0 and the workgroups
- * of one pass (256 threads, one pixel each, or a pixel pair each in bfloat16
- * storage with even P and a 4-byte aligned frame). */
+ * of its update pass (256 threads, one pixel each, or a pixel pair each in
+ * bfloat16 storage with even P and a 4-byte aligned frame); its reducing
+ * passes launch as many, but at most 1280, which then take several groups of
+ * pixels each. */
 typedef struct pros_launch_info {
   int32_t workgroups;        /* persistent workgroups of the frame kernel */
   int32_t threads;           /* threads per workgroup */
@@ -503,7 +505,7 @@ PROS_API pros_status pros_batch_set_dispatch(pros_batch* b, int32_t cooperative)
  * Synchronises; the tile (rows per thread) is kept.  On a streamed handle
  * (frames beyond the resident tiles) both schedules are accepted in either
  * storage type and run the same pass, which reads U once per CG step and forms
- * H on the matrix cores beside the gradient. */
+ * H in float64 on the matrix cores beside the gradient. */
 PROS_API pros_status pros_set_curvature(pros_handle* h, int32_t schedule);
 
 /* ---------------------------------------------------------------------------

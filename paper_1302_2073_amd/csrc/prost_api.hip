@@ -77,9 +77,8 @@ using namespace prost_host;
 // the handle's pinned host buffer with the header in front of it.  As a fill,
 // a median with one pixel per thread (nine byte loads each) and a copy, plus
 // two blocking copies for a host reader, a mask read cost 12 us of kernels and
-// 35-60 us of waiting: a frame with its mask on the host took 104 us at
-// 80x60x1 (k = 5) and takes 67, 16 frames of 160x120x3 (k = 15) with their
-// masks on the device 1 214 and 1 081 us, 8 of 640x480x3 925 and 845 us.
+// 35-60 us of waiting; now it is this kernel (4 us at 80x60x1, 8 at 1280x720)
+// and one wait.
 // The kernel is bound by its launch and one memory latency.  A thread takes four
 // pixels: with W a multiple of 4 they share a row, and the labels (0 or 1, a
 // byte each) are added as packed bytes, three 32-bit words and six edge bytes
@@ -922,7 +921,7 @@ pros_status pros_get_stats(pros_handle* h, pros_stats* out) {
 
 pros_status pros_get_launch_info(pros_handle* h, pros_launch_info* out) {
   if (!h || !out) return fail(PROS_EINVAL, "NULL argument");
-  if (h->streamed) {   // one launch per pass: no register tile, no gang exchange
+  if (h->streamed) {   // no register tile, no gang exchange; the update pass's groups
     // bfloat16 with even P takes pixel pairs (for 4-byte aligned frames)
     const bool pairs = h->prm.storage == PROS_BF16 && h->P % 2 == 0 && h->ldU % 2 == 0;
     out->threads = 256;
@@ -993,7 +992,7 @@ pros_status pros_set_curvature(pros_handle* h, int32_t schedule) {
   pros_status st = check_usable(h);
   if (st != PROS_OK) return st;
   if (schedule != 0 && schedule != 1) return fail(PROS_EINVAL, "curvature schedule must be 0 or 1");
-  if (h->streamed) {   // one launch per pass: both schedules, any storage, no exchange slots
+  if (h->streamed) {   // the same pass for both schedules, any storage, no exchange slots
     HIP_TRY(hipStreamSynchronize(h->stream));
     h->curv = schedule;
     return PROS_OK;

@@ -14,13 +14,15 @@
 //   for each CG step j:  A: g = -U^T(w phi'(r)), f = sum w phi(r)
 //                        B: d^T H d = sum w c(r) (u.d)^2
 //   eta pass:            a = U^T eta, ||eta||^2, f at the final y
-// The 3x3 median of a frame's labels runs at the start of the next launch
-// (or in mask_kernel when the mask is asked for first), which saves the
-// exchange that would otherwise separate the label writes from the median.
+// The 3x3 median of a frame's labels runs in the next frame, in the wavefronts
+// that do not wait in its first single-value exchange (at its start where the
+// weights come from it; in mask_kernel when the mask is asked for first), which
+// saves the exchange that would otherwise separate the label writes from it.
 // Every workgroup reduces the published partials in the same fixed order, so
 // all of them hold bit-identical k-vectors without a broadcast step.  Waiting
 // workgroups spin on epoch-tagged float64 slots (each thread on its own
-// values, no barrier inside the wait, bounded by a wall-clock time-out).
+// values, no barrier inside the wait, bounded by one wall-clock time-out per
+// exchange).
 #pragma once
 
 #include <utility>

@@ -406,7 +406,7 @@ __global__ __launch_bounds__(256) void qr_apply_f64(double* __restrict__ A, long
   __syncthreads();
   for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < m; e += (long long)gridDim.x * 256) {
     int z = 0;
-    asm volatile("" : "+v"(z));   // keeps the reads of M in the loop (see gram_apply)
+    asm volatile("" : "+v"(z));   // keeps the reads of M in the loop (K K / 2 doubles would not fit the registers)
     const double* Ml = &M[0][0] + z;
     double a[K];
 #pragma unroll

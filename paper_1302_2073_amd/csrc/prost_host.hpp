@@ -44,7 +44,7 @@ struct pros_handle {
   // frames too large for a resident gang: every pass streams U (prost_stream.hip)
   bool streamed = false;
   void* stream_ws = nullptr;    // k-space state, per-entry w c and eta, per-workgroup partials
-  int stream_blocks = 0;        // workgroups of a streamed pass
+  int stream_groups = 0;        // groups of 256 pixels of a streamed frame
   // host bookkeeping
   long long submitted = 0;
   bool state_set = false;

@@ -641,7 +641,7 @@ pros_status prost_stream_alloc(pros_handle* h) {
   if (e != hipSuccess) return prost_host::set_error(PROS_ENOMEM, "streamed-frame buffers: %s", hipGetErrorString(e));
   e = hipMemsetAsync(h->stream_ws, 0, bytes, h->stream);
   if (e != hipSuccess) return prost_host::set_error(PROS_EHIP, "streamed-frame buffers: %s", hipGetErrorString(e));
-  h->stream_blocks = nchunk;
+  h->stream_groups = nchunk;
   return PROS_OK;
 }
 
@@ -659,9 +659,9 @@ pros_status prost_stream_frame(pros_handle* h, const prost::FrameArgs& a) {
     if (pair)
       st_frame_class<uint16_t, true>(kc, a, ks, eta, part, (h->P / 2 + kStBlock - 1) / kStBlock, h->stream);
     else
-      st_frame_class<uint16_t, false>(kc, a, ks, eta, part, h->stream_blocks, h->stream);
+      st_frame_class<uint16_t, false>(kc, a, ks, eta, part, h->stream_groups, h->stream);
   } else {
-    st_frame_class<float, false>(kc, a, ks, eta, part, h->stream_blocks, h->stream);
+    st_frame_class<float, false>(kc, a, ks, eta, part, h->stream_groups, h->stream);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {

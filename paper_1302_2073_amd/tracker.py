@@ -225,7 +225,8 @@ class Tracker:
 
     def set_curvature(self, schedule):
         """0: d^T H d in a second pass per CG step; 1: H reduced with the
-        gradient (one exchange per step, float32 storage)."""
+        gradient (one exchange per step, float32 storage).  A streamed
+        handle takes either in any storage and runs one pass for both."""
         L.check(L.lib().pros_set_curvature(self._h, int(schedule)))
 
 
