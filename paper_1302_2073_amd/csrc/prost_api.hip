@@ -944,10 +944,11 @@ pros_status pros_get_launch_info(pros_handle* h, pros_launch_info* out) {
 }
 
 // Clear the exchange slots and restart the epoch and arrival counters (after
-// any change of the gang; stale tags must never match a new epoch).
+// any change of the gang; stale tags must never match a new epoch).  The mask's
+// flag goes with them: the next frame forms the median again.
 pros_status prost_host::reset_exchange(pros_handle* h) {
   HIP_TRY(hipMemsetAsync(h->part, 0, prost_host::part_bytes(h, h->G), h->stream));
-  HIP_TRY(hipMemsetAsync(h->sync, 0, 16, h->stream));
+  HIP_TRY(hipMemsetAsync(h->sync, 0, 24, h->stream));
   HIP_TRY(hipStreamSynchronize(h->stream));
   return PROS_OK;
 }

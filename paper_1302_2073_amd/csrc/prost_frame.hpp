@@ -54,7 +54,8 @@ struct FrameArgs {
   pros_stats* stats;     // statistics of the frame
   double* part;          // (2 * G + kExtraSlots) * kSlot doubles of workgroup partials
   unsigned* sync;        // [0] arrival counter, [1] counter base, [2] error bits, [3] epoch base,
-                         // [4] 1: the mask already is the median of the labels (mask_kernel)
+                         // [4] 1: the mask already is the median of the labels (mask_kernel),
+                         // [5] rejected frames since the epochs last went back (frame_epochs)
   long long ldU;
   int m, P, C, W, H, k;
   int G, tpw;
@@ -138,7 +139,7 @@ struct FrameSmem {
 
 // Diagnostics: wall-clock timestamp `idx` (< 64) of a tile, by thread 0.
 __device__ __forceinline__ void trace_point(const FrameArgs& a, int tile, int idx) {
-  if (a.trace && thread_index() == 0 && idx < 64) a.trace[(size_t)tile * 64 + idx] = wall_clock64();
+  if (a.trace && thread_index() == 0 && (unsigned)idx < 64u) a.trace[(size_t)tile * 64 + idx] = wall_clock64();
 }
 
 // Waits for component `comp` of the tagged slots q = row0, row0 + rs, ...
@@ -751,6 +752,7 @@ struct TileCtx {
   unsigned base, ebase;   // exchange counter / epoch bases of this launch
   long long n;            // frame index
   bool lead;              // tile 0 writes the stream's statistics and y
+  int rejected;           // rejected frames since the epochs last went back
   int median;             // the previous frame's median of this tile is still to be formed:
                           // 1 from labels of an earlier launch, 2 of this launch
 };
@@ -768,6 +770,8 @@ __device__ __forceinline__ TileCtx tile_begin(const FrameArgs& a, const int tile
   t.nq = t.npx * a.C;
   t.base = __hip_atomic_load(&a.sync[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   t.ebase = __hip_atomic_load(&a.sync[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  t.rejected = __builtin_amdgcn_readfirstlane(
+      (int)__hip_atomic_load(&a.sync[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   t.n = *a.nframe;
   t.lead = (tile == 0);
   if (tid < K) {
@@ -1221,6 +1225,21 @@ __device__ __forceinline__ void write_labels(const FrameArgs& a, const uint8_t* 
   }
 }
 
+// The exchange count at the end of a frame.  A rejected frame takes one exchange,
+// and the values that only a whole frame exchanges keep the tags of the last one.
+// Tags repeat after 256 exchanges, so a run of rejected frames goes round in four
+// epochs: the slots of its exchanges then never hold the tag that comes next (a
+// set is written every second exchange), and the others' tags stay recent.  The
+// same in every workgroup.
+constexpr int kRejectedEpochs = 4;
+__device__ __forceinline__ void frame_epochs(const FrameArgs& a, TileCtx& t, bool bad, int& nbar) {
+  t.rejected = __builtin_amdgcn_readfirstlane(bad) ? t.rejected + 1 : 0;   // scalar, as the count is
+  if (t.rejected == kRejectedEpochs && a.sync_mode != 0) {   // the counter has no tags, and only counts up
+    nbar -= kRejectedEpochs;
+    t.rejected = 0;
+  }
+}
+
 // Statistics, frame counter, y and the exchange bases for the next launch.
 __device__ __forceinline__ void tile_end(const FrameArgs& a, const int tile, KSpace<kMaxK>& ks, const TileCtx& t,
                                          int steps, int restarts, bool bad, int nbar) {
@@ -1244,9 +1263,10 @@ __device__ __forceinline__ void tile_end(const FrameArgs& a, const int tile, KSp
     }
     if (a.G == 1) {
       // a one-workgroup gang used no slots or counters: the bases stay
-    } else if (a.sync_mode != 0)
+    } else if (a.sync_mode != 0) {
       __hip_atomic_store(&a.sync[3], t.ebase + (unsigned)nbar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else
+      __hip_atomic_store(&a.sync[5], (unsigned)t.rejected, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else
       __hip_atomic_store(&a.sync[1], t.base + (unsigned)a.G * (unsigned)nbar, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -1511,6 +1531,7 @@ __device__ __forceinline__ bool frame_tile(const FrameArgs& a, const int tile, F
     write_labels<SEQ>(a, s_flag, ctx.p0, ctx.npx);
     trace_point(a, tile, 62);
   }
+  frame_epochs(a, ctx, bad, nbar);
   tile_end(a, tile, ks, ctx, steps, restarts, bad, nbar);
   if (!SEQ || ++fi >= a.nseq) break;
 
@@ -2047,6 +2068,7 @@ __device__ __forceinline__ bool frame_tile_packed(const FrameArgs& a, const int 
     write_labels<SEQ>(a, s_flag, ctx.p0, ctx.npx);
     trace_point(a, tile, 62);
   }
+  frame_epochs(a, ctx, bad, nbar);
   tile_end(a, tile, ks, ctx, steps, restarts, bad, nbar);
   if (!SEQ || NL > 0 || ++fi >= a.nseq) break;   // sequences: register tiles only
 
