@@ -418,19 +418,33 @@ static pros_status pick_launch(pros_handle* h, int force_nr) {
   return PROS_OK;
 }
 
+// The sequence form of the chosen tile.  It keeps the tile between frames and
+// takes more registers for it, so it can hold fewer workgroups per compute unit
+// than the frame kernel: such a gang goes frame by frame.
+static pros_status pick_sequence(pros_handle* h) {
+  h->kfn_seq = h->streamed ? nullptr : prost::frame_kernel_seq(h->prm.storage == PROS_BF16, h->k, h->NR);
+  if (!h->kfn_seq) return PROS_OK;
+  int occ = 0;
+  HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, h->kfn_seq, prost::kBlock, 0));
+  if (h->G > (long long)occ * h->num_cu) h->kfn_seq = nullptr;
+  return PROS_OK;
+}
+
 // The launch of a handle whose tile (force_nr) or features have changed; what is
 // refused leaves it as it was.  Schedule 1 is taken by streamed handles of either
 // storage type, but the tile kernels that reduce H are float32.
 static pros_status choose_launch(pros_handle* h, int force_nr) {
   const bool streamed = h->streamed;
-  const void* kfn = h->kfn;
+  const void *kfn = h->kfn, *kfn_seq = h->kfn_seq;
   const int NR = h->NR, G = h->G, tpw = h->tpw;
   pros_status st = pick_launch(h, force_nr);
+  if (st == PROS_OK) st = pick_sequence(h);
   if (st == PROS_OK && !h->streamed && h->curv == 1 && h->prm.storage != PROS_F32)
     st = fail(PROS_EUNSUPPORTED, "curvature schedule 1 needs float32 storage (or the streamed form)");
   if (st != PROS_OK) {
     h->streamed = streamed;
     h->kfn = kfn;
+    h->kfn_seq = kfn_seq;
     h->NR = NR;
     h->G = G;
     h->tpw = tpw;
@@ -856,7 +870,7 @@ pros_status pros_track_frames(pros_handle* h, const void* const* frames, int32_t
   // frames that depend on more than the tile's own state between frames
   // (filtered-mask weights, pre-processing statistics, scores, the wide
   // exchange) run one launch each
-  const void* fseq = h->streamed ? nullptr : prost::frame_kernel_seq(h->prm.storage == PROS_BF16, h->k, h->NR);
+  const void* fseq = h->streamed ? nullptr : h->kfn_seq;
   const bool seq_ok = fseq && !h->prm.weights_from_filtered && h->pre_mean == nullptr && h->score == nullptr &&
                       !wide_exchange(h);
   if (!seq_ok) {
