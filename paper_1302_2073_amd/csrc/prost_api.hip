@@ -391,7 +391,12 @@ static pros_status pick_launch(pros_handle* h, int force_nr) {
     const long long G = (h->P + tpw - 1) / tpw;
     int occ = 0;
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, f, prost::kBlock, 0));
-    if (G > (long long)occ * h->num_cu) continue;   // not resident
+    if (G > (long long)occ * h->num_cu) {           // not resident with all its registers
+      f = prost::frame_kernel_dense(h->prm.storage == PROS_BF16, h->k, NR, ext);
+      if (!f) continue;
+      HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, f, prost::kBlock, 0));
+      if (G > (long long)occ * h->num_cu) continue;
+    }
     best = f; bestNR = NR; bestG = (int)G; bestT = tpw;
     if (G <= h->num_cu) break;                      // smallest tile at one workgroup per CU
   }

@@ -2139,8 +2139,55 @@ __device__ __forceinline__ bool run_tile(const FrameArgs& a, const int tile, Fra
   }
 }
 
-template <int K, int NR, typename TS, bool EXT, bool SEQ = false>
-__global__ __launch_bounds__(kBlock, 2) void frame_kernel(FrameArgs a) {
+// Workgroups of a frame kernel that a compute unit holds: 4, 3 and 2 up to the
+// given k, else 1.
+struct PerUnit {
+  int four, three, two;
+};
+constexpr int per_unit(const PerUnit& u, int K) { return K <= u.four ? 4 : K <= u.three ? 3 : K <= u.two ? 2 : 1; }
+// Without a register limit: all loads of a tile are in flight before any is used.
+template <int NR, typename TS, bool EXT>
+constexpr PerUnit wide_per_unit() {
+  if constexpr (sizeof(TS) == 4) {
+    if constexpr (EXT)
+      return NR == 1 ? PerUnit{0, 0, 16} : NR == 2 ? PerUnit{0, 0, 11} : NR == 4 ? PerUnit{0, 0, 7}
+           : NR == 8 ? PerUnit{0, 0, 1} : PerUnit{0, 0, 0};
+    else
+      return NR == 1 ? PerUnit{0, 16, 16} : NR == 2 ? PerUnit{0, 6, 16} : NR == 4 ? PerUnit{0, 1, 14}
+           : NR == 8 ? PerUnit{0, 0, 6} : PerUnit{0, 0, 1};
+  } else {
+    if constexpr (EXT)
+      return NR == 2 ? PerUnit{0, 4, 16} : NR == 4 ? PerUnit{0, 0, 16} : NR == 8 ? PerUnit{0, 0, 6} : PerUnit{0, 0, 0};
+    else
+      return NR == 2 ? PerUnit{0, 9, 16} : NR == 4 ? PerUnit{0, 1, 16} : NR == 8 ? PerUnit{0, 0, 8} : PerUnit{0, 0, 0};
+  }
+}
+// With one.  A gang must be resident as a whole, so these times the compute units
+// are the largest gangs that pros_set_launch accepts.  The limit costs up to 4 %
+// of a frame (160x120x3, k = 15, float32 33.4 and 34.9 us; 640x480x3, k = 9,
+// bfloat16 48.4 and 49.9), so a kernel of its own has it, for the gangs that need it.
+template <int NR, typename TS, bool EXT>
+constexpr PerUnit dense_per_unit() {
+  if constexpr (sizeof(TS) == 4) {
+    if constexpr (EXT)
+      return NR == 1 ? PerUnit{3, 7, 16} : NR == 2 ? PerUnit{0, 5, 16} : NR == 4 ? PerUnit{0, 2, 8}
+           : NR == 8 ? PerUnit{0, 0, 3} : PerUnit{0, 0, 0};
+    else
+      return NR == 1 ? PerUnit{10, 16, 16} : NR == 2 ? PerUnit{4, 11, 16} : NR == 4 ? PerUnit{0, 4, 15}
+           : NR == 8 ? PerUnit{0, 0, 6} : PerUnit{0, 0, 1};
+  } else {
+    if constexpr (EXT)
+      return NR == 2 ? PerUnit{5, 15, 16} : NR == 4 ? PerUnit{0, 8, 16} : NR == 8 ? PerUnit{0, 2, 11}
+           : NR == 16 ? PerUnit{0, 0, 3} : PerUnit{0, 0, 0};
+    else
+      return NR == 2 ? PerUnit{10, 15, 16} : NR == 4 ? PerUnit{2, 9, 16} : NR == 8 ? PerUnit{0, 2, 12}
+           : NR == 16 ? PerUnit{0, 0, 3} : PerUnit{0, 0, 0};
+  }
+}
+
+// WGS: workgroups of a compute unit that the registers are limited for (1: no limit).
+template <int K, int NR, typename TS, bool EXT, bool SEQ = false, int WGS = 1>
+__global__ __launch_bounds__(kBlock, WGS * kWaves / 4) void frame_kernel(FrameArgs a) {
   __shared__ FrameSmem sm;
   run_tile<K, NR, TS, EXT, EXT, 0, SEQ>(a, blockIdx.x, sm);
 }
