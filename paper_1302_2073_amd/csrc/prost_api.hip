@@ -335,8 +335,9 @@ bool prost_host::pair_layout(const pros_handle* h) {
 // (its gang-wide exchanges), so the fastest tile is the smallest one whose
 // gang still fits one workgroup per compute unit: more rows per thread only
 // add work per workgroup.  Small frames are the exception: a gang of up to
-// kSmallGang workgroups exchanges faster than a larger one (measured at
-// 160x120x3: 29 workgroups 74 us per frame, 113 workgroups 81 us), so the
+// kSmallGang workgroups exchanges faster than a larger one (160x120x3, k = 15,
+// exchange 3, ordinary dispatch: 29 workgroups 32.9 us per frame, 57 31.1, 113
+// 33.6; the line was drawn where they took 74 and 81 us, 29 and 113), so the
 // smallest tile reaching such a gang wins, and a frame that fits one
 // workgroup takes that tile (its reductions stay inside the workgroup, no
 // memory round trip).  Frames too large for one workgroup per CU take the
@@ -425,13 +426,17 @@ static pros_status pick_launch(pros_handle* h, int force_nr) {
 
 // The sequence form of the chosen tile.  It keeps the tile between frames and
 // takes more registers for it, so it can hold fewer workgroups per compute unit
-// than the frame kernel: such a gang goes frame by frame.
+// than the frame kernel: such a gang goes frame by frame.  Asked for by the first
+// sequence (the question loads the kernel).
 static pros_status pick_sequence(pros_handle* h) {
-  h->kfn_seq = h->streamed ? nullptr : prost::frame_kernel_seq(h->prm.storage == PROS_BF16, h->k, h->NR);
-  if (!h->kfn_seq) return PROS_OK;
-  int occ = 0;
-  HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, h->kfn_seq, prost::kBlock, 0));
-  if (h->G > (long long)occ * h->num_cu) h->kfn_seq = nullptr;
+  if (h->seq_known) return PROS_OK;
+  h->kfn_seq = prost::frame_kernel_seq(h->prm.storage == PROS_BF16, h->k, h->NR);
+  if (h->kfn_seq) {
+    int occ = 0;
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, h->kfn_seq, prost::kBlock, 0));
+    if (h->G > (long long)occ * h->num_cu) h->kfn_seq = nullptr;
+  }
+  h->seq_known = true;
   return PROS_OK;
 }
 
@@ -440,20 +445,19 @@ static pros_status pick_sequence(pros_handle* h) {
 // storage type, but the tile kernels that reduce H are float32.
 static pros_status choose_launch(pros_handle* h, int force_nr) {
   const bool streamed = h->streamed;
-  const void *kfn = h->kfn, *kfn_seq = h->kfn_seq;
+  const void* kfn = h->kfn;
   const int NR = h->NR, G = h->G, tpw = h->tpw;
   pros_status st = pick_launch(h, force_nr);
-  if (st == PROS_OK) st = pick_sequence(h);
   if (st == PROS_OK && !h->streamed && h->curv == 1 && h->prm.storage != PROS_F32)
     st = fail(PROS_EUNSUPPORTED, "curvature schedule 1 needs float32 storage (or the streamed form)");
   if (st != PROS_OK) {
     h->streamed = streamed;
     h->kfn = kfn;
-    h->kfn_seq = kfn_seq;
     h->NR = NR;
     h->G = G;
     h->tpw = tpw;
   }
+  h->seq_known = false;
   return st;
 }
 
@@ -510,7 +514,10 @@ pros_status prost_host::create_handle(const pros_params* prm, hipStream_t stream
     st = choose_launch(h, nr_force);
     if (st != PROS_OK) return bail(st);
     // small gangs: every workgroup reading all partials beats the two hops
-    // (160x120x3 at 29 workgroups: 74 vs 84 us; 320x240x3 at 113: 91 vs 85)
+    // (us per frame, exchange 3 and 2, ordinary dispatch: 160x120x3, k = 15 at 29
+    // workgroups 32.9 and 39.7, 320x240x3, k = 10 at 57 39.8 and 45.9, at 113 37.6
+    // and 41.4, at 226 43.5 and 38.6).  Where it lies between 32 and 128 does not
+    // matter: the gangs chosen here have up to 32 workgroups or more than 128.
     h->sync_mode = h->G <= 64 ? 3 : 2;
   }
   const size_t es = (prm->storage == PROS_BF16) ? 2 : 4;
@@ -875,6 +882,10 @@ pros_status pros_track_frames(pros_handle* h, const void* const* frames, int32_t
   // frames that depend on more than the tile's own state between frames
   // (filtered-mask weights, pre-processing statistics, scores, the wide
   // exchange) run one launch each
+  if (!h->streamed) {
+    st = pick_sequence(h);
+    if (st != PROS_OK) return st;
+  }
   const void* fseq = h->streamed ? nullptr : h->kfn_seq;
   const bool seq_ok = fseq && !h->prm.weights_from_filtered && h->pre_mean == nullptr && h->score == nullptr &&
                       !wide_exchange(h);

@@ -34,6 +34,7 @@ struct pros_handle {
   // launch configuration
   const void* kfn = nullptr;
   const void* kfn_seq = nullptr;   // the sequence form; NULL: none is built, or it holds no gang of G workgroups
+  bool seq_known = false;          // kfn_seq is that of the present tile
   int G = 0, tpw = 0, NR = 0;
   int sync_mode = 2;       // 0: counter barrier, 1: tagged gather/broadcast, 2: two-level tagged, 3: tagged all-read
   int curv = 0;            // CG curvature schedule: 0 = second pass per step, 1 = H with the gradient
