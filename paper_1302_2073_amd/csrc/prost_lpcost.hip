@@ -61,7 +61,7 @@ __device__ __forceinline__ void stage_rows(const float* __restrict__ U, long lon
 // dealt to the 8 XCDs in turn).  The partial sums are laid out by output, one
 // float64 per block, so that the blocks of a 128-byte line then meet in one L2
 // instead of each writing 8 bytes of it to memory (27 MB of them in a backward
-// over 921600 rows, k = 15, 64 frames: 203 us without this order, 189 with it).
+// over 921600 rows, k = 15, 64 frames, which takes 7 % less with this order).
 __device__ __forceinline__ int lp_block() {
   const int n = gridDim.x, x = blockIdx.x & 7, per = n >> 3, rem = n & 7;
   return x * per + min(x, rem) + (int)(blockIdx.x >> 3);
@@ -118,9 +118,9 @@ __device__ __forceinline__ void arrived(const float (&y)[K]) {
 // and a smaller exponent carries a smaller rounding error.  Per frame the
 // workgroup's sum of w phi(r) is formed with one in-place reduce-scatter per
 // pass and float64 across wavefronts.  Partials: part[b * nblk + block].
-// Bound by the reads of X (rows, k, frames: 921600, 15, 64: 130 us with
-// its finishing launch when y came from LDS, now 83, 3.6 TB/s; 230400, 10, 32:
-// 17.3, now 16.7).
+// Bound by the vector instructions beside the read of X (rows, k, frames:
+// 921600, 15, 64: 84 us in repeated passes, 134 when y came from LDS, and 61 for
+// the bytes at the copy rate; 230400, 10, 32: 13.5).
 template <int K, int FORM>
 __global__ __launch_bounds__(kLpBlock) void lpcost_fwd_kernel(const float* __restrict__ U, const float* __restrict__ Y,
                                                               const float* __restrict__ X, const float* __restrict__ w,
@@ -193,10 +193,11 @@ __global__ __launch_bounds__(kLpBlock) void lpcost_fwd_kernel(const float* __res
 // in the forward kernel.  The rows of U are staged through the buffer that
 // holds s afterwards, once for the thread's own row and once as the matrix
 // operand, which stays in registers: half the LDS, written once per entry and
-// read 16 bytes at a time.  Bound by its reads and writes of X and dX
-// (rows, k, frames: 921600, 15, 64: 260 us with its finishing launch, now 182,
-// 3.4 TB/s; 230400, 10, 32: 27.1 and 28).  One frame's coefficients at a time:
-// two at a time spill scalar registers here.  Partials (output q = b K + j of dY,
+// read 16 bytes at a time.  Bound by the vector instructions beside its reads
+// and writes of X and dX (rows, k, frames: 921600, 15, 64: 155 us in repeated
+// passes, 248 before, and 123 for the bytes at the copy rate; 230400, 10, 32:
+// 23.9 both).  One frame's coefficients at a time: two at a time spill scalar
+// registers here.  Partials (output q = b K + j of dY,
 // then dmu at q = B K): part[q * nblk + block].
 template <int K, int FORM>
 __global__ __launch_bounds__(kLpBlock) void lpcost_bwd_kernel(const float* __restrict__ U, const float* __restrict__ Y,
