@@ -30,7 +30,9 @@ def _hadamard(k):
 @pytest.mark.parametrize("schedule", [0, 1])
 @pytest.mark.parametrize("width,height,channels,k,storage", [(640, 480, 3, 15, "f32"), (1280, 240, 1, 4, "f32"),
                                                              (640, 480, 3, 16, "f32"), (640, 480, 3, 4, "bf16"),
-                                                             (641, 481, 1, 16, "bf16"), (640, 480, 3, 16, "bf16")])
+                                                             (641, 481, 1, 16, "bf16"), (640, 480, 3, 16, "bf16"),
+                                                             (640, 480, 3, 2, "f32"), (640, 480, 3, 5, "f32"),
+                                                             (640, 480, 3, 8, "f32"), (640, 480, 3, 10, "f32")])
 def test_step_along_a_direction_of_foreground_pixels(width, height, channels, k, storage, schedule):
     """The background is fitted exactly (r = 0, weight 1, the largest c), so g comes from the foreground pixels alone
     (weight 5e-5), along a direction that every background row of U is orthogonal to: exactly for the dyadic rotations
@@ -66,7 +68,7 @@ def test_step_along_a_direction_of_foreground_pixels(width, height, channels, k,
     assert np.linalg.norm(y - new.y) <= TOL_Y * np.linalg.norm(new.y)
 
 
-@pytest.mark.parametrize("k", [1, 16])
+@pytest.mark.parametrize("k", [1, 5, 8, 16])
 @pytest.mark.parametrize("storage", ["f32", "bf16"])
 def test_sums_over_many_pixel_groups(storage, k):
     """p = 2 and one constant column (the others 0): y is the mean of x over u, with x = 2^13 in the first third of the
